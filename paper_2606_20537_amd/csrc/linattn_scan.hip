@@ -706,17 +706,12 @@ __global__ __launch_bounds__(NT) void linattn_scan_kernel(const ScanParams p) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
 
-    // workgroup -> (head, slice); slices of one head share an XCD (and its L2)
-    // when the grid allows it (workgroups go round-robin over 8 XCDs).
     Ctx x;
     x.H = p.H;
     x.dv = p.dv;
-    const int NS = x.dv / DVS;
-    const int N = x.H * NS;
-    int logical = blockIdx.x;
-    if ((N % 8) == 0 && ((N / 8) % NS) == 0) logical = (blockIdx.x % 8) * (N / 8) + blockIdx.x / 8;
-    x.h = logical / NS;
-    x.j0 = (logical % NS) * DVS;
+    int slice;
+    if (!head_slice(blockIdx.x, x.H, x.dv / DVS, x.h, slice)) return;
+    x.j0 = slice * DVS;
     x.lane = tid & 63;
     x.li = x.lane & 15;
     x.grp = x.lane >> 4;
@@ -746,7 +741,7 @@ __global__ __launch_bounds__(NT) void linattn_scan_kernel(const ScanParams p) {
 
 template <int DK, bool F32>
 hipError_t launch_t(const ScanParams& p, hipStream_t stream) {
-    const unsigned grid = (unsigned)(p.H * (p.dv / DVS));
+    const unsigned grid = head_slice_grid(p.H, p.dv / DVS);
     const void* fn = p.T <= CH ? reinterpret_cast<const void*>(&linattn_scan_kernel<DK, F32, true, true>)
                      : p.chunk_states ? reinterpret_cast<const void*>(&linattn_scan_kernel<DK, F32, false, true>)
                                       : reinterpret_cast<const void*>(&linattn_scan_kernel<DK, F32, false, false>);
