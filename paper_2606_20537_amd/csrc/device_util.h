@@ -100,6 +100,29 @@ __device__ inline void split_n(const float* f, V& hi, V& lo) {
     }
 }
 
+// The same split of products f w: each is rounded once for hi and enters lo
+// exactly (one fma).  Written out, so that kernels that must agree bit for bit
+// do not depend on where the compiler contracts f w - hi.
+template <int N, typename V>
+__device__ inline void split_product(const float* f, const float* w, V& hi, V& lo) {
+    static_assert(N % 2 == 0, "pairs");
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    #pragma unroll
+    for (int e = 0; e < N; e += 2) {
+        const bf16x2 h = __builtin_convertvector((f32x2){f[e] * w[e], f[e + 1] * w[e + 1]}, bf16x2);
+        const uint32_t u = __builtin_bit_cast(uint32_t, h);
+        const float h0 = __builtin_bit_cast(float, u << 16);
+        const float h1 = __builtin_bit_cast(float, u & 0xFFFF0000u);
+        const bf16x2 l = __builtin_convertvector(
+            (f32x2){__builtin_fmaf(f[e], w[e], -h0), __builtin_fmaf(f[e + 1], w[e + 1], -h1)}, bf16x2);
+        hi[e] = h[0];
+        hi[e + 1] = h[1];
+        lo[e] = l[0];
+        lo[e + 1] = l[1];
+    }
+}
+
 // Workgroup -> (head, slice of the head's work) for kernels in which the
 // workgroups of a head read the same lines.  Workgroups go round-robin over
 // the 8 XCDs, each with an L2 of its own, so XCD b % 8 takes all slices of an

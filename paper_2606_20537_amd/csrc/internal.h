@@ -86,6 +86,8 @@ struct ScanParams {
 int validate_linattn(const linattn_args* a, ScanParams* out);
 
 hipError_t launch_linattn_scan(const ScanParams& p, hipStream_t stream);
+// the same call in segments of the sequence (T > 64), the same bits
+hipError_t launch_linattn_seg(const ScanParams& p, hipStream_t stream);
 // T == 1, bf16 inputs (a decode step); same contract as launch_linattn_scan
 hipError_t launch_linattn_step(const ScanParams& p, hipStream_t stream);
 
