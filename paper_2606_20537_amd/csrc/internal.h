@@ -132,7 +132,7 @@ hipError_t launch_gdn_step(const GdnParams& p, hipStream_t stream);
 // first_block[s + 1].  Quantize multiplies by mul[s] (1 / scale) before
 // encoding; dequantize multiplies the decoded value by mul[s] (scale).
 constexpr int kFp8MaxSeg = 64;
-constexpr int kFp8GroupsPerBlock = 512;  // 256 threads x 2 groups of 16 elements
+constexpr int kFp8GroupsPerBlock = 256;  // 256 threads x 2 units of 8 elements
 
 struct Fp8Params {
     uint64_t src[kFp8MaxSeg];
