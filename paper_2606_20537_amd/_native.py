@@ -142,6 +142,12 @@ def _addr(x):
 def _stream(s):
     if s is None:
         import torch
+        # torch.cuda.current_stream() builds a Stream object: 3.0 us of the 7.8 us
+        # that a decode step took the host, against 0.3 us for the handle alone.
+        # Without an initialised device it does the initialisation, or raises
+        # (a forked child).
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(s, int):
         return s
