@@ -17,7 +17,8 @@
 //     sum of tile counts once, in LDS, and finds its tile's buffer by a
 //     binary search in LDS;
 //   * fork reads each vector once and stores it to every destination set;
-//     gather gives each environment ("rep") its own source arena.
+//     gather gives each environment ("rep") its own source arena, or, of
+//     several large capsules, up to four environments of one capsule to a rep.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -58,14 +59,16 @@ __device__ inline uint32_t last_le(const uint32_t* a, uint32_t n, uint32_t x) {
 
 // kThreads threads of kUnroll 16-byte vectors each form one tile; kPtr
 // destination pointers (buffers x destination sets) fit in LDS.
-template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr>
+// GATHER: the destinations of a rep, up to 64, are looked up per tile, one in
+// each lane, instead of in an LDS table.
+template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr, bool GATHER>
 __global__ __launch_bounds__(kThreads) void capsule_copy_kernel(const CopyParams p) {
     constexpr uint32_t kTileVec = (uint32_t)kThreads * kUnroll;
     constexpr int kPer = (kMaxSeg + 1 + kThreads - 1) / kThreads;  // table entries per thread
     __shared__ uint64_t s_start[kMaxSeg + 1];  // capsule vector offset of buffer i
     __shared__ uint32_t s_tile[kMaxSeg + 1];   // first tile of buffer i
     __shared__ uint32_t s_wave[kThreads / 64];
-    __shared__ uint64_t s_ptr[kPtr];           // live pointers of the current rep
+    __shared__ uint64_t s_ptr[GATHER ? 1 : kPtr];  // live pointers of the call's sets
 
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63, wave = tid >> 6;
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(kThreads) void capsule_copy_kernel(const CopyParams
     for (uint64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const uint32_t rep = (uint32_t)(t / tiles_per_rep);
         const uint32_t lt = (uint32_t)(t - (uint64_t)rep * tiles_per_rep);
-        if ((int64_t)rep != cur_rep) {  // block-uniform
+        if (!GATHER && (int64_t)rep != cur_rep) {  // block-uniform
             __syncthreads();
             if (p.mode == kLiveToArena) {
                 for (uint32_t i = tid; i < n; i += kThreads) s_ptr[i] = p.tabs[0][i].ptr;
@@ -142,7 +145,26 @@ __global__ __launch_bounds__(kThreads) void capsule_copy_kernel(const CopyParams
         const bool full = lim >= kTileVec;
         const uint32_t last = (uint32_t)((full ? (uint64_t)kTileVec : lim) - 1);
 
-        if (p.mode == kLiveToArena) {
+        if constexpr (GATHER) {
+            const uint32_t first = p.first[rep], cnt = p.first[rep + 1] - first;
+            const uint64_t mine = lane < cnt ? p.tabs[first + lane][seg].ptr : 0;
+            const u32x4* src = reinterpret_cast<const u32x4*>(p.arena_in[rep]) + s0 + off;
+            #pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                const uint32_t i = u * kThreads + tid;
+                data[u] = ld16<NT_LD>(src + (i < last ? i : last));
+            }
+            for (uint32_t d = 0; d < cnt; ++d) {
+                const uint32_t plo = __builtin_amdgcn_readlane((uint32_t)mine, d);
+                const uint32_t phi = __builtin_amdgcn_readlane((uint32_t)(mine >> 32), d);
+                u32x4* dst = reinterpret_cast<u32x4*>((uint64_t)phi << 32 | plo) + off;
+                #pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    const uint32_t i = u * kThreads + tid;
+                    if (full || i <= last) st16<NT_ST>(dst + i, data[u]);
+                }
+            }
+        } else if (p.mode == kLiveToArena) {
             const u32x4* src = reinterpret_cast<const u32x4*>(s_ptr[seg]) + off;
             u32x4* dst = reinterpret_cast<u32x4*>(p.arena_out) + s0 + off;
             #pragma unroll
@@ -204,13 +226,19 @@ uint64_t tiles_of(const CopyParams& p) {
     return (p.nvec / (s.threads * s.unroll) + p.n_seg) * p.n_rep;
 }
 
-template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr>
+template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr, bool GATHER = false>
 hipError_t launch_t(const CopyParams& p, hipStream_t stream) {
-    return launch_kernel(reinterpret_cast<const void*>(&capsule_copy_kernel<kThreads, kUnroll, NT_LD, NT_ST, kPtr>),
+    return launch_kernel(reinterpret_cast<const void*>(&capsule_copy_kernel<kThreads, kUnroll, NT_LD, NT_ST, kPtr, GATHER>),
                          dim3((unsigned)tiles_of(p)), dim3(kThreads), p, stream);
 }
 
 }  // namespace
+
+uint64_t gather_tiles(const CopyParams& p) {
+    CopyParams one = p;
+    one.n_rep = 1;
+    return tiles_of(one);
+}
 
 bool copy_params_ok(const CopyParams& p) {
     if (p.nvec == 0 || p.n_rep == 0) return true;
@@ -231,11 +259,14 @@ hipError_t launch_copy(const CopyParams& p, int num_cus, hipStream_t stream) {
     //  * gather-restore: 16 KiB tiles with cached loads, so that a gallery
     //    small enough for the 256 MB Infinity Cache stays there across resets,
     //    and streamed stores, so that the environments' bytes do not evict it
-    //    (-14 % per reset against cached stores).
+    //    (-14 % per reset against cached stores); of several large capsules in
+    //    the order of the capsules, several environments to a block (the host
+    //    decides, see capsule_gather_restore).
     // Only fork keeps several destination pointer tables in LDS; the other
     // verbs size that table for one set, which leaves room for eight blocks
     // per CU.
     if (p.n_dst > 1) return launch_t<512, 1, true, true, kMaxPtrLds>(p, stream);
+    if (p.mode == kGather) return launch_t<256, 4, false, true, kMaxSeg, true>(p, stream);
     if (p.n_rep > 1) return launch_t<256, 4, false, true, kMaxSeg>(p, stream);
     return launch_t<256, 4, true, true, kMaxSeg>(p, stream);
 }

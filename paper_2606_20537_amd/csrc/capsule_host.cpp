@@ -472,6 +472,10 @@ int capsule_fork(cap_capsule cap, const cap_set* lives, uint32_t n, uint64_t pre
     });
 }
 
+constexpr uint64_t kL2Bytes = 4 << 20;  // of an XCD
+// two rounds of the eight blocks that a CU holds
+constexpr uint64_t kGatherBlocks = 2 * 8 * 256;
+
 int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery, const int32_t* ids,
                            const cap_set* lives, uint32_t n_env, void* stream) {
     return guarded([&]() -> int {
@@ -509,21 +513,46 @@ int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery, const
         int rc = current_device_matches(lives[0]);
         if (rc != CAP_OK) return rc;
         const uint32_t n_seg = (uint32_t)lives[0]->bufs.size();
+        // environments in the order of their capsules: those of one capsule that
+        // fall into one launch read it once
+        std::vector<uint32_t> order(n_env);
+        for (uint32_t e = 0; e < n_env; ++e) order[e] = e;
+        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ids[a] < ids[b]; });
         std::vector<cap::CopyParams> launches;
         for (uint32_t first = 0; first < n_env; first += cap::kMaxRep) {
             const uint32_t cnt = std::min<uint32_t>(cap::kMaxRep, n_env - first);
             cap::CopyParams p{};
-            p.layout = lives[first]->dtab;
-            for (uint32_t r = 0; r < cnt; ++r) {
-                p.tabs[r] = lives[first + r]->dtab;
-                p.arena_in[r] = static_cast<const uint8_t*>(gallery[ids[first + r]]->arena);
-            }
+            p.layout = lives[order[first]]->dtab;
+            for (uint32_t r = 0; r < cnt; ++r) p.tabs[r] = lives[order[first + r]]->dtab;
             p.P = c0->P_aligned;
             p.nvec = c0->bytes / 16;
             p.n_seg = n_seg;
             p.n_dst = 1;
-            p.n_rep = cnt;
-            p.mode = cap::kArenaToLive;
+            uint32_t n_src = 1;
+            for (uint32_t r = 1; r < cnt; ++r) n_src += ids[order[first + r]] != ids[order[first + r - 1]];
+            // Reps: at most `share` environments of one capsule each; a block
+            // stores its tile to all of them.  Four (us, 32 environments of 8
+            // capsules of 8.4 MB: 1 each 66.5, 2 64.2, 4 58.8, 8 58.2, in the
+            // caller's order 77.2; 48 of 2 of 17 MB: 141.1, 140.8, 141.3, 142.1,
+            // 167.2), halved while the launch has fewer than kGatherBlocks
+            // blocks, so that a small capsule's stores do not queue up in a few.
+            // Sources that an XCD's L2 holds, or a single one, which no order
+            // brings closer, keep a rep to each environment and the pointer table
+            // in LDS (48 of 1 of 17 MB: 136, shared by four 156; 48 of 2 of 1.9 MB:
+            // 24.0 and 25.0).
+            const bool shared = n_src > 1 && n_src * c0->bytes > kL2Bytes;
+            p.mode = shared ? cap::kGather : cap::kArenaToLive;
+            for (uint32_t share = shared ? 4 : 1;; share /= 2) {
+                p.n_rep = 0;
+                for (uint32_t r = 0, in_rep = 0; r < cnt; ++r, ++in_rep)
+                    if (r == 0 || in_rep == share || ids[order[first + r]] != ids[order[first + r - 1]]) {
+                        p.first[p.n_rep] = (uint8_t)r;
+                        p.arena_in[p.n_rep++] = static_cast<const uint8_t*>(gallery[ids[order[first + r]]]->arena);
+                        in_rep = 0;
+                    }
+                p.first[p.n_rep] = (uint8_t)cnt;
+                if (share == 1 || p.n_rep * cap::gather_tiles(p) >= kGatherBlocks) break;
+            }
             if (!cap::copy_params_ok(p)) return CAP_E_SIZE;
             launches.push_back(p);
         }

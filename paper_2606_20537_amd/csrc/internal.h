@@ -35,17 +35,19 @@ struct SegEntry {
     uint64_t b;
 };
 
-constexpr int kMaxRep = 64;   // sources (gather environments) per launch
+constexpr int kMaxRep = 64;   // destination sets of a gather per launch
 constexpr int kMaxDst = 16;   // destinations per source (fork)
 constexpr int kMaxPtrLds = 2048;  // live pointers one copy block holds in LDS
 
-enum CopyMode : int { kLiveToArena = 0, kArenaToLive = 1 };
+enum CopyMode : int { kLiveToArena = 0, kArenaToLive = 1, kGather = 2 };
 
 // Per-launch arguments of the copy kernel, passed by value.
 //   kLiveToArena : rep 0 copies set `tabs[0]` -> arena_out.
 //   kArenaToLive : rep r copies arena_in[r] -> n_dst destination sets
-//                  tabs[r * n_dst + d] (fork: one rep, n_dst sets;
-//                  gather: n_rep reps, one set each).
+//                  tabs[r * n_dst + d] (fork: one rep, n_dst sets; a gather
+//                  of little source: n_rep reps, one set each).
+//   kGather      : rep r copies arena_in[r] -> the sets tabs[first[r]] ..
+//                  tabs[first[r + 1] - 1].
 struct CopyParams {
     const SegEntry* layout;            // any table of the call (shared a, b)
     const SegEntry* tabs[kMaxRep];
@@ -57,8 +59,11 @@ struct CopyParams {
     uint32_t        n_dst;
     uint32_t        n_rep;
     int32_t         mode;
+    uint8_t         first[kMaxRep + 1];
 };
 
+// Blocks a gather of the capsule p describes takes for each rep.
+uint64_t gather_tiles(const CopyParams& p);
 // Whether launch_copy accepts p (grid and LDS-table limits); a multi-launch
 // call checks every launch with it before enqueueing the first one.
 bool copy_params_ok(const CopyParams& p);
