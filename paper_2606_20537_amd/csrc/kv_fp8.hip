@@ -40,6 +40,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ inline float bits_f32(uint32_t u) { return __builtin_bit_cast(float, u); }
+__device__ inline uint32_t sign_bit(float x) { return __builtin_bit_cast(uint32_t, x) & 0x80000000u; }
 
 // +-448 for anything larger, infinities included; NaN stays.
 __device__ inline float saturate(float x) {
@@ -95,11 +96,14 @@ __global__ __launch_bounds__(256) void fp8_kernel(const Fp8Params p) {
                 #pragma unroll
                 for (int w = 0; w < 2; ++w)
                     out[w] = encode2<true>(in[u][2 * w + 1], mul, encode2<false>(in[u][2 * w], mul, 0u));
-                if (any_zero(~out[0]) || any_zero(~out[1])) {  // NaN codes take their inputs' signs
+                // NaN codes take the signs of the products (zero times the
+                // infinite reciprocal of a tiny scale is a NaN of its own sign)
+                if (any_zero(~out[0]) || any_zero(~out[1])) {
                     #pragma unroll
                     for (int w = 0; w < 2; ++w) {
                         const uint32_t a = in[u][2 * w], b = in[u][2 * w + 1], nan = zero_bytes(~out[w]);
-                        const uint32_t sign = (a >> 8 & 0x80u) | (a >> 16 & 0x8000u) | (b << 8 & 0x800000u) | (b & 0x80000000u);
+                        const uint32_t sign = sign_bit(bits_f32(a << 16) * mul) >> 24 | sign_bit(bits_f32(a & 0xFFFF0000u) * mul) >> 16 |
+                                              sign_bit(bits_f32(b << 16) * mul) >> 8 | sign_bit(bits_f32(b & 0xFFFF0000u) * mul);
                         out[w] = (out[w] & ~nan) | (sign & nan);
                     }
                 }

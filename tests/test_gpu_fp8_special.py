@@ -28,3 +28,14 @@ def test_mixed_specials(orc, n, scale):
     got, back = dst.cpu().numpy(), out.cpu().numpy().view(np.uint16)
     assert np.array_equal(got[:n], orc.fp8_quantize(bits, scale)) and np.all(got[n:] == 0xAA)
     assert np.array_equal(back[:n], orc.fp8_dequantize(codes, scale)) and np.all(back[n:] == 0x1234)
+
+
+@pytest.mark.parametrize("scale", [1e-39, 1e-45, 3e-39])
+def test_reciprocal_out_of_range(orc, scale):
+    """1 / scale is infinite for the first two: zeros become NaN with the sign
+    of the product (not the input's), everything else saturates."""
+    bits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    dst = torch.full((65536,), 0xAA, dtype=torch.uint8, device="cuda")
+    cap.kv_fp8_quantize([(torch.from_numpy(bits.view(np.int16).copy()).cuda(), dst, 65536, scale)])
+    torch.cuda.synchronize()
+    assert np.array_equal(dst.cpu().numpy(), orc.fp8_quantize(bits, scale))
