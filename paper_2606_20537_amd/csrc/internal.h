@@ -139,6 +139,13 @@ hipError_t launch_gdn_step(const GdnParams& p, hipStream_t stream);
 constexpr int kFp8MaxSeg = 64;
 constexpr int kFp8GroupsPerBlock = 256;  // 256 threads x 2 units of 8 elements
 
+// A launch counts its threads along x in 32 bits: 2^24 - 1 blocks of 256, which
+// 6.9e10 elements pass (206 GB on both sides).  So block b is (b % kFp8GridX,
+// b / kFp8GridX); the blocks past the last one find no elements.
+constexpr uint32_t kFp8GridX = 1u << 22;
+inline uint32_t fp8_grid_x(uint32_t blocks) { return blocks < kFp8GridX ? blocks : kFp8GridX; }
+inline uint32_t fp8_grid_y(uint32_t blocks) { return (blocks + kFp8GridX - 1) / kFp8GridX; }
+
 struct Fp8Params {
     uint64_t src[kFp8MaxSeg];
     uint64_t dst[kFp8MaxSeg];

@@ -77,10 +77,11 @@ __device__ inline uint32_t segment_of(const Fp8Params& p, uint32_t b) {
 
 template <bool QUANT>
 __global__ __launch_bounds__(256) void fp8_kernel(const Fp8Params p) {
-    const uint32_t s = __builtin_amdgcn_readfirstlane(segment_of(p, blockIdx.x));
+    const uint32_t block = blockIdx.y * kFp8GridX + blockIdx.x;
+    const uint32_t s = __builtin_amdgcn_readfirstlane(segment_of(p, block));
     const uint64_t n = 2 * p.n_groups[s];  // units
     constexpr int kU = 2 * kFp8GroupsPerBlock / 256;
-    const uint64_t u0 = (uint64_t)(blockIdx.x - p.first_block[s]) * (256 * kU) + threadIdx.x;
+    const uint64_t u0 = (uint64_t)(block - p.first_block[s]) * (256 * kU) + threadIdx.x;
     const float mul = p.mul[s];
     if (QUANT) {
         const u32x4* src = reinterpret_cast<const u32x4*>(p.src[s]);
@@ -147,7 +148,7 @@ hipError_t launch_fp8(const Fp8Params& p, hipStream_t stream) {
     if (blocks == 0) return hipSuccess;
     const void* fn = p.quantize ? reinterpret_cast<const void*>(&fp8_kernel<true>)
                                 : reinterpret_cast<const void*>(&fp8_kernel<false>);
-    return launch_kernel(fn, dim3(blocks), dim3(256), p, stream);
+    return launch_kernel(fn, dim3(fp8_grid_x(blocks), fp8_grid_y(blocks)), dim3(256), p, stream);
 }
 
 }  // namespace cap
