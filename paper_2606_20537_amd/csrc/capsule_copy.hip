@@ -17,8 +17,8 @@
 //     sum of tile counts once, in LDS, and finds its tile's buffer by a
 //     binary search in LDS;
 //   * fork reads each vector once and stores it to every destination set;
-//     gather gives each environment ("rep") its own source arena, or, of
-//     several large capsules, up to four environments of one capsule to a rep.
+//     gather gives each environment ("rep") its own source arena, or, where
+//     it stores much, up to four environments of one capsule to a rep.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -259,9 +259,9 @@ hipError_t launch_copy(const CopyParams& p, int num_cus, hipStream_t stream) {
     //  * gather-restore: 16 KiB tiles with cached loads, so that a gallery
     //    small enough for the 256 MB Infinity Cache stays there across resets,
     //    and streamed stores, so that the environments' bytes do not evict it
-    //    (-14 % per reset against cached stores); of several large capsules in
-    //    the order of the capsules, several environments to a block (the host
-    //    decides, see capsule_gather_restore).
+    //    (-14 % per reset against cached stores); of several capsules and many
+    //    bytes in the order of the capsules, several environments to a block
+    //    (the host decides, see capsule_gather_restore).
     // Only fork keeps several destination pointer tables in LDS; the other
     // verbs size that table for one set, which leaves room for eight blocks
     // per CU.

@@ -472,7 +472,6 @@ int capsule_fork(cap_capsule cap, const cap_set* lives, uint32_t n, uint64_t pre
     });
 }
 
-constexpr uint64_t kL2Bytes = 4 << 20;  // of an XCD
 // two rounds of the eight blocks that a CU holds
 constexpr uint64_t kGatherBlocks = 2 * 8 * 256;
 
@@ -513,11 +512,13 @@ int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery, const
         int rc = current_device_matches(lives[0]);
         if (rc != CAP_OK) return rc;
         const uint32_t n_seg = (uint32_t)lives[0]->bufs.size();
-        // environments in the order of their capsules: those of one capsule that
-        // fall into one launch read it once
+        // Launches that store much go through the environments in the order of
+        // their capsules, so that those of one capsule read it once; the others in
+        // the caller's order.
         std::vector<uint32_t> order(n_env);
         for (uint32_t e = 0; e < n_env; ++e) order[e] = e;
-        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ids[a] < ids[b]; });
+        if (cap::gather_shares(std::min<uint32_t>(cap::kMaxRep, n_env), c0->bytes))
+            std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ids[a] < ids[b]; });
         std::vector<cap::CopyParams> launches;
         for (uint32_t first = 0; first < n_env; first += cap::kMaxRep) {
             const uint32_t cnt = std::min<uint32_t>(cap::kMaxRep, n_env - first);
@@ -536,11 +537,11 @@ int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery, const
             // caller's order 77.2; 48 of 2 of 17 MB: 141.1, 140.8, 141.3, 142.1,
             // 167.2), halved while the launch has fewer than kGatherBlocks
             // blocks, so that a small capsule's stores do not queue up in a few.
-            // Sources that an XCD's L2 holds, or a single one, which no order
-            // brings closer, keep a rep to each environment and the pointer table
-            // in LDS (48 of 1 of 17 MB: 136, shared by four 156; 48 of 2 of 1.9 MB:
-            // 24.0 and 25.0).
-            const bool shared = n_src > 1 && n_src * c0->bytes > kL2Bytes;
+            // Launches that store little (gather_shares), and those of a single
+            // capsule, which no order brings closer, keep a rep to each
+            // environment and the pointer table in LDS (48 of 1 of 17 MB: 136,
+            // shared by four 156).
+            const bool shared = n_src > 1 && cap::gather_shares(cnt, c0->bytes);
             p.mode = shared ? cap::kGather : cap::kArenaToLive;
             for (uint32_t share = shared ? 4 : 1;; share /= 2) {
                 p.n_rep = 0;

@@ -45,7 +45,7 @@ enum CopyMode : int { kLiveToArena = 0, kArenaToLive = 1, kGather = 2 };
 //   kLiveToArena : rep 0 copies set `tabs[0]` -> arena_out.
 //   kArenaToLive : rep r copies arena_in[r] -> n_dst destination sets
 //                  tabs[r * n_dst + d] (fork: one rep, n_dst sets; a gather
-//                  of little source: n_rep reps, one set each).
+//                  that stores little: n_rep reps, one set each).
 //   kGather      : rep r copies arena_in[r] -> the sets tabs[first[r]] ..
 //                  tabs[first[r + 1] - 1].
 struct CopyParams {
@@ -62,6 +62,14 @@ struct CopyParams {
     uint8_t         first[kMaxRep + 1];
 };
 
+// Whether a launch of a gather that stores `bytes` to each of n environments
+// shares its reads between them.  Only above 128 MB, where the lookups per tile
+// pay (us, destinations in turn, a rep to each environment / shared: 16
+// environments of 2.4 MB 10.9 / 14.6, 40 of 1.2 MB 15.3 / 17.7, 31 of 3.5 MB 31.0 /
+// 31.7, 24 of 4.7 MB, 113 MB in all, 33.5 / 34.8; 31 of 4.7 MB, 146 MB, 42.1 / 35.1,
+// 16 of 9.4 MB 45.5 / 36.8, 64 of 4.7 MB 84.0 / 59.4).
+constexpr uint64_t kGatherShareBytes = 128 << 20;
+inline bool gather_shares(uint32_t n, uint64_t bytes) { return n * bytes > kGatherShareBytes; }
 // Blocks a gather of the capsule p describes takes for each rep.
 uint64_t gather_tiles(const CopyParams& p);
 // Whether launch_copy accepts p (grid and LDS-table limits); a multi-launch

@@ -1,6 +1,7 @@
 """Gather with several environments of one capsule: how many a block serves
-follows from the sizes (4, 2 or 1); every environment holds its capsule's
-bytes and nothing past the boundary changes."""
+follows from the sizes (up to 4, 2 or 1 in launches that store more than
+128 MB, 1 otherwise); every environment holds its capsule's bytes and nothing
+past the boundary changes."""
 import pytest
 import torch
 
@@ -13,12 +14,16 @@ CASES = [
     # (row bytes, environments' ids, gallery): a capsule is 2 P rows and a small state
     (16, [0, 0, 0, 1, 1, 0], 2),                # a few tiles: a rep to each environment
     (65552, [0] * 17, 1),                       # one capsule: the same
-    (8208, [1, 1, 0, 0, 0], 2),                 # 4.21 MB in all, just past the 4 MiB: one each
-    (8160, [1, 1, 0, 0, 0], 2),                 # 4.19 MB, just below
-    (65552, [3, 0, 3, 1, 1, 3, 0, 3, 3], 4),    # 16.8 MB, uneven, one capsule unused
-    (131088, [0] * 17 + [1] * 18 + [0], 2),     # 33.6 MB: fours, twos and a rest
-    (24592, [i % 2 for i in range(63)] + [0, 1, 1], 2),  # 66: a second launch, of one capsule
+    (8208, [1, 1, 0, 0, 0], 2),                 # 10.5 MB in all: the same
+    (8160, [1, 1, 0, 0, 0], 2),
+    (65552, [3, 0, 3, 1, 1, 3, 0, 3, 3], 4),    # 16.8 MB each, 151 MB in all, uneven, one capsule unused: 2, 2, 4 and 1
+    (131088, [0] * 17 + [1] * 18 + [0], 2),     # 33.6 MB each: fours and rests of 2
+    (24592, [i % 2 for i in range(63)] + [0, 1, 1], 2),  # 66: fours, then a second launch, of one capsule
     (24592, [i % 3 for i in range(65)], 3),     # a second launch of one
+    (24592, [i % 2 for i in range(32)], 2),     # 201 MB: pairs (3096 blocks at four each)
+    (8208, [i % 3 for i in range(63)], 3),      # 132.7 MB, just below 128 MiB: one each, in the caller's order
+    (8208, [i % 3 for i in range(64)], 3),      # 134.8 MB, just above: pairs
+    (8208, [i % 3 for i in range(70)], 3),      # and a second launch that stores little
 ]
 
 
