@@ -21,6 +21,8 @@
 //     it stores much, up to four environments of one capsule to a rep.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace cap {
@@ -62,7 +64,7 @@ __device__ inline uint32_t last_le(const uint32_t* a, uint32_t n, uint32_t x) {
 // GATHER: the destinations of a rep, up to 64, are looked up per tile, one in
 // each lane, instead of in an LDS table.
 template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr, bool GATHER>
-__global__ __launch_bounds__(kThreads) void capsule_copy_kernel(const CopyParams p) {
+__global__ __launch_bounds__(kThreads) void capsule_copy_kernel(const std::conditional_t<GATHER, GatherParams, CopyParams> p) {
     constexpr uint32_t kTileVec = (uint32_t)kThreads * kUnroll;
     constexpr int kPer = (kMaxSeg + 1 + kThreads - 1) / kThreads;  // table entries per thread
     __shared__ uint64_t s_start[kMaxSeg + 1];  // capsule vector offset of buffer i
@@ -226,9 +228,9 @@ uint64_t tiles_of(const CopyParams& p) {
     return (p.nvec / (s.threads * s.unroll) + p.n_seg) * p.n_rep;
 }
 
-template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr, bool GATHER = false>
+template <int kThreads, int kUnroll, bool NT_LD, bool NT_ST, int kPtr>
 hipError_t launch_t(const CopyParams& p, hipStream_t stream) {
-    return launch_kernel(reinterpret_cast<const void*>(&capsule_copy_kernel<kThreads, kUnroll, NT_LD, NT_ST, kPtr, GATHER>),
+    return launch_kernel(reinterpret_cast<const void*>(&capsule_copy_kernel<kThreads, kUnroll, NT_LD, NT_ST, kPtr, false>),
                          dim3((unsigned)tiles_of(p)), dim3(kThreads), p, stream);
 }
 
@@ -266,9 +268,13 @@ hipError_t launch_copy(const CopyParams& p, int num_cus, hipStream_t stream) {
     // verbs size that table for one set, which leaves room for eight blocks
     // per CU.
     if (p.n_dst > 1) return launch_t<512, 1, true, true, kMaxPtrLds>(p, stream);
-    if (p.mode == kGather) return launch_t<256, 4, false, true, kMaxSeg, true>(p, stream);
     if (p.n_rep > 1) return launch_t<256, 4, false, true, kMaxSeg>(p, stream);
     return launch_t<256, 4, true, true, kMaxSeg>(p, stream);
+}
+
+hipError_t launch_gather(const GatherParams& p, hipStream_t stream) {
+    return launch_kernel(reinterpret_cast<const void*>(&capsule_copy_kernel<256, 4, false, true, kMaxSeg, true>),
+                         dim3((unsigned)tiles_of(p)), dim3(256), p, stream);
 }
 
 }  // namespace cap

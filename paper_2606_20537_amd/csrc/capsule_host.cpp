@@ -515,22 +515,28 @@ int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery, const
         // Launches that store much go through the environments in the order of
         // their capsules, so that those of one capsule read it once; the others in
         // the caller's order.
-        std::vector<uint32_t> order(n_env);
-        for (uint32_t e = 0; e < n_env; ++e) order[e] = e;
-        if (cap::gather_shares(std::min<uint32_t>(cap::kMaxRep, n_env), c0->bytes))
+        std::vector<uint32_t> order;
+        if (cap::gather_shares(std::min<uint32_t>(cap::kMaxRep, n_env), c0->bytes)) {
+            for (uint32_t e = 0; e < n_env; ++e) order.push_back(e);
             std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ids[a] < ids[b]; });
-        std::vector<cap::CopyParams> launches;
+        }
+        std::vector<cap::GatherParams> launches;
         for (uint32_t first = 0; first < n_env; first += cap::kMaxRep) {
             const uint32_t cnt = std::min<uint32_t>(cap::kMaxRep, n_env - first);
-            cap::CopyParams p{};
-            p.layout = lives[order[first]]->dtab;
-            for (uint32_t r = 0; r < cnt; ++r) p.tabs[r] = lives[order[first + r]]->dtab;
+            auto env = [&](uint32_t r) { return order.empty() ? first + r : order[first + r]; };
+            auto same = [&](uint32_t r) { return ids[env(r)] == ids[env(r - 1)]; };
+            cap::GatherParams p{};
+            p.layout = lives[env(0)]->dtab;
+            for (uint32_t r = 0; r < cnt; ++r) {
+                p.tabs[r] = lives[env(r)]->dtab;
+                p.arena_in[r] = static_cast<const uint8_t*>(gallery[ids[env(r)]]->arena);
+            }
             p.P = c0->P_aligned;
             p.nvec = c0->bytes / 16;
             p.n_seg = n_seg;
             p.n_dst = 1;
-            uint32_t n_src = 1;
-            for (uint32_t r = 1; r < cnt; ++r) n_src += ids[order[first + r]] != ids[order[first + r - 1]];
+            p.n_rep = cnt;
+            p.mode = cap::kArenaToLive;
             // Reps: at most `share` environments of one capsule each; a block
             // stores its tile to all of them.  Four (us, 32 environments of 8
             // capsules of 8.4 MB: 1 each 66.5, 2 64.2, 4 58.8, 8 58.2, in the
@@ -541,24 +547,27 @@ int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery, const
             // capsule, which no order brings closer, keep a rep to each
             // environment and the pointer table in LDS (48 of 1 of 17 MB: 136,
             // shared by four 156).
-            const bool shared = n_src > 1 && cap::gather_shares(cnt, c0->bytes);
-            p.mode = shared ? cap::kGather : cap::kArenaToLive;
-            for (uint32_t share = shared ? 4 : 1;; share /= 2) {
-                p.n_rep = 0;
-                for (uint32_t r = 0, in_rep = 0; r < cnt; ++r, ++in_rep)
-                    if (r == 0 || in_rep == share || ids[order[first + r]] != ids[order[first + r - 1]]) {
-                        p.first[p.n_rep] = (uint8_t)r;
-                        p.arena_in[p.n_rep++] = static_cast<const uint8_t*>(gallery[ids[order[first + r]]]->arena);
-                        in_rep = 0;
-                    }
-                p.first[p.n_rep] = (uint8_t)cnt;
-                if (share == 1 || p.n_rep * cap::gather_tiles(p) >= kGatherBlocks) break;
+            if (cap::gather_shares(cnt, c0->bytes) && ids[env(0)] != ids[env(cnt - 1)]) {
+                p.mode = cap::kGather;
+                for (uint32_t share = 4;; share /= 2) {
+                    p.n_rep = 0;
+                    for (uint32_t r = 0, in_rep = 0; r < cnt; ++r, ++in_rep)
+                        if (r == 0 || in_rep == share || !same(r)) {
+                            p.first[p.n_rep] = (uint8_t)r;
+                            p.arena_in[p.n_rep++] = static_cast<const uint8_t*>(gallery[ids[env(r)]]->arena);
+                            in_rep = 0;
+                        }
+                    p.first[p.n_rep] = (uint8_t)cnt;
+                    if (share == 1 || p.n_rep * cap::gather_tiles(p) >= kGatherBlocks) break;
+                }
             }
             if (!cap::copy_params_ok(p)) return CAP_E_SIZE;
             launches.push_back(p);
         }
-        for (const cap::CopyParams& p : launches) {
-            rc = launch_status(cap::launch_copy(p, lives[0]->num_cus, static_cast<hipStream_t>(stream)));
+        for (const cap::GatherParams& p : launches) {
+            rc = launch_status(p.mode == cap::kGather
+                                   ? cap::launch_gather(p, static_cast<hipStream_t>(stream))
+                                   : cap::launch_copy(p, lives[0]->num_cus, static_cast<hipStream_t>(stream)));
             if (rc != CAP_OK) return rc;
         }
         for (uint32_t e = 0; e < n_env; ++e) {

@@ -59,7 +59,12 @@ struct CopyParams {
     uint32_t        n_dst;
     uint32_t        n_rep;
     int32_t         mode;
-    uint8_t         first[kMaxRep + 1];
+};
+
+// A kGather launch.  `first` is an argument of that kernel only, so that the
+// other copies do not pass it along.
+struct GatherParams : CopyParams {
+    uint8_t first[kMaxRep + 1];
 };
 
 // Whether a launch of a gather that stores `bytes` to each of n environments
@@ -77,6 +82,8 @@ uint64_t gather_tiles(const CopyParams& p);
 bool copy_params_ok(const CopyParams& p);
 // Launch the descriptor-driven copy.  Returns hipSuccess or the launch error.
 hipError_t launch_copy(const CopyParams& p, int num_cus, hipStream_t stream);
+// The same for mode kGather.
+hipError_t launch_gather(const GatherParams& p, hipStream_t stream);
 
 // Scan arguments after host validation (sizes as 64-bit, pointers raw).
 struct ScanParams {
