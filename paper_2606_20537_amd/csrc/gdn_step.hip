@@ -29,11 +29,14 @@ __global__ __launch_bounds__(2 * DK) void gdn_step_kernel(const GdnParams p) {
     constexpr int NW = 2 * DK / 64;  // waves
     __shared__ float part[NW][2][17];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // the slices of a head share an XCD (and its L2), since neighbouring ones
-    // read the two halves of the same 128-byte state lines
-    int h, slice;
-    if (!head_slice(blockIdx.x, p.H, p.dv / DVS, h, slice)) return;
-    const int j0 = slice * DVS;
+    // workgroup -> (head, slice); the slices of a head share an XCD (and its
+    // L2), since neighbouring slices read the two halves of the same
+    // 128-byte state lines (workgroups go round-robin over 8 XCDs)
+    const int NS = p.dv / DVS;
+    const int N = p.H * NS;
+    int logical = blockIdx.x;
+    if ((N % 8) == 0 && ((N / 8) % NS) == 0) logical = (blockIdx.x % 8) * (N / 8) + blockIdx.x / 8;
+    const int h = logical / NS, j0 = (logical % NS) * DVS;
     const int d = tid >> 1, half = tid & 1, c0 = 8 * half;
     const int64_t sidx = ((int64_t)h * DK + d) * p.dv + j0 + c0;  // element of S[h][d][j0 + c0]
 
@@ -109,7 +112,7 @@ __global__ __launch_bounds__(2 * DK) void gdn_step_kernel(const GdnParams p) {
 }  // namespace
 
 hipError_t launch_gdn_step(const GdnParams& p, hipStream_t stream) {
-    const unsigned grid = head_slice_grid(p.H, p.dv / DVS);
+    const unsigned grid = (unsigned)(p.H * (p.dv / DVS));
     if (p.T != 1) return hipErrorInvalidValue;
     if (p.dk == 128) return launch_kernel(reinterpret_cast<const void*>(&gdn_step_kernel<128>), dim3(grid), dim3(256), p, stream);
     if (p.dk == 64) return launch_kernel(reinterpret_cast<const void*>(&gdn_step_kernel<64>), dim3(grid), dim3(128), p, stream);

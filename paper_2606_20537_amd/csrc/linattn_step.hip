@@ -29,11 +29,15 @@ __global__ __launch_bounds__(2 * DK) void linattn_step_kernel(const ScanParams p
     constexpr int NW = 2 * DK / 64;  // waves
     __shared__ float part[NW][2][9];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // the slices of a head share an XCD (and its L2), since neighbouring ones
-    // read the two halves of the same 128-byte state lines
-    int h, slice;
-    if (!head_slice(blockIdx.x, p.H, p.dv / DVS, h, slice)) return;
-    const int j0 = slice * DVS;
+    // workgroup -> (head, slice); the slices of a head share an XCD (and its
+    // L2) when the grid allows it, since neighbouring slices read the two
+    // halves of the same 128-byte state lines (workgroups go round-robin
+    // over 8 XCDs)
+    const int NS = p.dv / DVS;
+    const int N = p.H * NS;
+    int logical = blockIdx.x;
+    if ((N % 8) == 0 && ((N / 8) % NS) == 0) logical = (blockIdx.x % 8) * (N / 8) + blockIdx.x / 8;
+    const int h = logical / NS, j0 = (logical % NS) * DVS;
     const int d = tid >> 1, c0 = 8 * (tid & 1);
     const int64_t sidx = ((int64_t)h * DK + d) * p.dv + j0 + c0;  // element of S[h][d][j0 + c0]
 
@@ -98,7 +102,7 @@ __global__ __launch_bounds__(2 * DK) void linattn_step_kernel(const ScanParams p
 }  // namespace
 
 hipError_t launch_linattn_step(const ScanParams& p, hipStream_t stream) {
-    const unsigned grid = head_slice_grid(p.H, p.dv / DVS);
+    const unsigned grid = (unsigned)(p.H * (p.dv / DVS));
     if (p.in_f32 || p.T != 1) return hipErrorInvalidValue;
     if (p.dk == 128)
         return launch_kernel(reinterpret_cast<const void*>(&linattn_step_kernel<128>), dim3(grid), dim3(256), p, stream);
