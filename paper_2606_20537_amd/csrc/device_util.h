@@ -123,34 +123,6 @@ __device__ inline void split_product(const float* f, const float* w, V& hi, V& l
     }
 }
 
-// Workgroup -> (head, slice of the head's work) for kernels in which the
-// workgroups of a head read the same lines.  Workgroups go round-robin over
-// the 8 XCDs, each with an L2 of its own, so XCD b % 8 takes all slices of an
-// eighth of the heads, neighbouring ones, also where 8 does not divide the
-// head count (the XCDs then differ by one head; false for the workgroups of
-// the missing ones).  Measured against slices dealt out one by one: delta-rule
-// prefill of 4000 tokens, 20 heads 126 -> 113 us, 28 heads 143 -> 115 us;
-// linear-attention prefill of 900 tokens, 28 heads 28.2 -> 22.9 us.  Where
-// that would leave the fullest XCD half as much again as its share they are
-// dealt out one by one (1 head, 900 tokens with chunk states: 20.4 us, on one
-// XCD 21.4; 10 heads x 256 columns, 300 tokens: 12.8 and 13.7).
-__host__ __device__ inline bool heads_by_xcd(int H) { return H >= 8 && (H + 7) / 8 * 16 <= 3 * H; }
-__host__ __device__ inline unsigned head_slice_grid(int H, int per) {
-    return (unsigned)(heads_by_xcd(H) ? (H + 7) / 8 * 8 : H) * (unsigned)per;
-}
-__device__ inline bool head_slice(unsigned b, int H, int per, int& h, int& slice) {
-    if (!heads_by_xcd(H)) {
-        h = (int)(b / (unsigned)per);
-        slice = (int)(b % (unsigned)per);
-        return true;
-    }
-    const int xcd = (int)(b % 8);
-    const int first = (int)((int64_t)xcd * H / 8), end = (int)((int64_t)(xcd + 1) * H / 8);
-    h = first + (int)(b / 8 / (unsigned)per);
-    slice = (int)(b / 8 % (unsigned)per);
-    return h < end;
-}
-
 // Workgroup barrier for LDS traffic only.  Global stores are never read back
 // inside the scans, so the barrier does not wait for them (a plain
 // __syncthreads() would drain every outstanding global access).

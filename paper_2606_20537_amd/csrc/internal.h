@@ -85,6 +85,40 @@ hipError_t launch_copy(const CopyParams& p, int num_cus, hipStream_t stream);
 // The same for mode kGather.
 hipError_t launch_gather(const GatherParams& p, hipStream_t stream);
 
+// Placement of kernels that take a CU for each workgroup and in which the
+// `per` workgroups of a head read the same lines.  Workgroups go round-robin
+// over the 8 XCDs, each with an L2 of its own.  By XCD, XCD b % 8 takes all
+// slices of an eighth of the heads, neighbouring ones (the XCDs differ by one
+// head where 8 does not divide the head count, and the workgroups of the
+// missing ones end at once); otherwise they are dealt out one by one.
+// Measured (us, dealt / by XCD): delta-rule prefill of 4000 tokens x 128
+// columns, 20 heads 126 / 113, 28 heads 143 / 115; linear-attention prefill of
+// 900 tokens, 28 heads 28.2 / 22.9.  Not by XCD
+//  * where the fullest XCD, of 32 CUs, would then need more rounds than the
+//    deal: delta-rule prefill of 4000 tokens, 17 heads x 192 columns 113 / 198,
+//    20 x 176 120 / 202; linear attention, 2048 tokens, 17 x 192 39.3 / 70.2;
+//  * where it would have half as much again as its share (1 head, 900 tokens
+//    with chunk states: 20.4 us, on one XCD 21.4; 10 heads x 256 columns, 300
+//    tokens: 12.8 and 13.7).
+inline bool heads_by_xcd(int H, int per) {
+    const int64_t most = (H + 7) / 8, dealt = ((int64_t)H * per + 7) / 8;  // heads, workgroups of the fullest XCD
+    return H >= 8 && most * 16 <= 3 * (int64_t)H && (most * per + 31) / 32 <= (dealt + 31) / 32;
+}
+inline unsigned head_slice_grid(int H, int per) {
+    return (unsigned)(heads_by_xcd(H, per) ? (H + 7) / 8 * 8 : H) * (unsigned)per;
+}
+struct HeadSlice {
+    int h, slice;
+    bool on;
+};
+__host__ __device__ inline HeadSlice head_slice(unsigned b, bool by_xcd, int H, int per) {
+    const unsigned q = by_xcd ? b / 8 : b, xcd = b % 8;
+    const int first = by_xcd ? (int)((uint64_t)xcd * (unsigned)H / 8) : 0;
+    const int end = by_xcd ? (int)((uint64_t)(xcd + 1) * (unsigned)H / 8) : H;
+    const int h = first + (int)(q / (unsigned)per);
+    return {h, (int)(q % (unsigned)per), h < end};
+}
+
 // Scan arguments after host validation (sizes as 64-bit, pointers raw).
 struct ScanParams {
     const void*  q;
@@ -99,6 +133,7 @@ struct ScanParams {
     int32_t      H, dk, dv;
     int32_t      in_f32;   // 1: q/k/v are fp32, 0: bf16
     float        scale;
+    int32_t      by_xcd;   // heads_by_xcd of the launch
 };
 
 // Host checks of a linattn_args (status codes as documented in capsule.h);
@@ -135,6 +170,7 @@ struct GdnParams {
     int64_t      T;
     int32_t      H, dk, dv;
     float        scale;
+    int32_t      by_xcd;  // heads_by_xcd of the launch
 };
 
 // Host checks of a gdn_args; need_ws: the call reads args->workspace (a

@@ -709,9 +709,10 @@ __global__ __launch_bounds__(NT) void linattn_scan_kernel(const ScanParams p) {
     Ctx x;
     x.H = p.H;
     x.dv = p.dv;
-    int slice;
-    if (!head_slice(blockIdx.x, x.H, x.dv / DVS, x.h, slice)) return;
-    x.j0 = slice * DVS;
+    const HeadSlice hs = head_slice(blockIdx.x, p.by_xcd, x.H, x.dv / DVS);
+    if (!hs.on) return;
+    x.h = hs.h;
+    x.j0 = hs.slice * DVS;
     x.lane = tid & 63;
     x.li = x.lane & 15;
     x.grp = x.lane >> 4;
@@ -740,8 +741,9 @@ __global__ __launch_bounds__(NT) void linattn_scan_kernel(const ScanParams p) {
 }
 
 template <int DK, bool F32>
-hipError_t launch_t(const ScanParams& p, hipStream_t stream) {
+hipError_t launch_t(ScanParams p, hipStream_t stream) {
     const unsigned grid = head_slice_grid(p.H, p.dv / DVS);
+    p.by_xcd = heads_by_xcd(p.H, p.dv / DVS);
     const void* fn = p.T <= CH ? reinterpret_cast<const void*>(&linattn_scan_kernel<DK, F32, true, true>)
                      : p.chunk_states ? reinterpret_cast<const void*>(&linattn_scan_kernel<DK, F32, false, true>)
                                       : reinterpret_cast<const void*>(&linattn_scan_kernel<DK, F32, false, false>);

@@ -182,8 +182,9 @@ __global__ __launch_bounds__(64 * kFoldWaves, 2) void linattn_fold_kernel(const 
 
     // workgroup -> (head, row block, columns)
     const int per = DB * (dv / 16);
-    int h, slice;
-    if (!head_slice(blockIdx.x, H, per, h, slice)) return;
+    const HeadSlice hs = head_slice(blockIdx.x, p.by_xcd, H, per);
+    if (!hs.on) return;
+    const int h = hs.h, slice = hs.slice;
     const int d0 = DA * (slice % DB), j0 = 16 * (slice / DB);
     const int64_t qk_row = (int64_t)H * DK * ES, v_row = (int64_t)H * dv * ES;
     const int nA = (sp.nseg - 1) * sp.G;             // chunks to fold, all full
@@ -843,10 +844,11 @@ hipError_t launch_seg(const SegParams& sp, hipStream_t stream) {
 }
 
 template <int DK, int DA, bool F32>
-hipError_t launch_fold(const SegParams& sp, hipStream_t stream) {
-    const ScanParams& p = sp.s;
+hipError_t launch_fold(SegParams sp, hipStream_t stream) {
+    const int per = (DK / DA) * (sp.s.dv / 16);
+    sp.s.by_xcd = heads_by_xcd(sp.s.H, per);
     return launch_kernel(reinterpret_cast<const void*>(&linattn_fold_kernel<DK, DA, F32>),
-                         dim3(head_slice_grid(p.H, (DK / DA) * (p.dv / 16))), dim3(64 * kFoldWaves), sp, stream);
+                         dim3(head_slice_grid(sp.s.H, per)), dim3(64 * kFoldWaves), sp, stream);
 }
 
 template <int DK, bool F32>
