@@ -107,6 +107,11 @@ inline bool heads_by_xcd(int H, int per) {
 inline unsigned head_slice_grid(int H, int per) {
     return (unsigned)(heads_by_xcd(H, per) ? (H + 7) / 8 * 8 : H) * (unsigned)per;
 }
+// Rounds that the fullest XCD then needs.
+inline int64_t scan_rounds(int H, int per) {
+    const int64_t most = heads_by_xcd(H, per) ? (int64_t)((H + 7) / 8) * per : ((int64_t)H * per + 7) / 8;
+    return (most + 31) / 32;
+}
 struct HeadSlice {
     int h, slice;
     bool on;
@@ -139,6 +144,76 @@ struct ScanParams {
 // Host checks of a linattn_args (status codes as documented in capsule.h);
 // on CAP_OK *out holds the launch parameters.
 int validate_linattn(const linattn_args* a, ScanParams* out);
+
+// Whether a linear-attention prefill runs in segments of the sequence
+// (linattn_seg.hip) or in one pass (linattn_scan.hip); both give the same bits.
+// In chunks n and in x, 4 for each head and 64 columns begun: while the pass
+// takes one round it takes 4.5 us + 0.98 us a chunk whatever x, the segments
+// 11 us + a rate that grows with x.  Measured at up to 64 heads x 256 columns
+// (pass / segments, us; in brackets the range of their ratio over all shapes
+// at a number of chunks, bf16 and dk 128 where nothing is said):
+//   x <= 64    1024 tokens x 8 heads x 128 columns 20.9 / 19.1 [1.01 to 1.13 at
+//              16]; dk 64 [1.00 to 1.21]; fp32, 512 tokens [1.04 to 1.12 at 8]
+//   x <= 128   2048 x 16 x 128 37.7 / 31.4 [from 0.83 at 16, from 1.00 at 28]; dk 64
+//              [up to x = 96 from 0.97 at 28, 1.04 at 32; beyond 0.96 at 32, 1.04 at
+//              48]; fp32 [from 0.98 at 28 with 32 heads x 64, else 1.01]
+//   x <= 144   [0.89 to 1.14 at 32, 1.01 to 1.32 at 64]; dk 64 [1.07 to 1.15 at 64]
+//   x <= 176   [0.94 to 1.19 at 64, 1.02 to 1.31 at 96]; dk 64 [0.99 to 1.06 at 64,
+//              1.07 to 1.16 at 128]
+//   x <= 256   [0.92 to 1.17 at 96, 0.98 to 1.30 at 128]; dk 64 [0.93 to 1.18 at 128,
+//              1.01 to 1.40 at 256]; 16384 x 16 x 128 256 / 153, x 32 288 / 260
+//   two rounds [up to x = 384 0.99 to 1.22 at 32; beyond 0.98 to 1.06 at 32, 1.00 to
+//              1.23 at 64]; dk 64 [up to 384 1.04 to 1.21 at 48; beyond 0.95 to 1.11
+//              at 64, 1.08 to 1.29 at 128]
+//   more       [1.02 to 1.28 at 32]; dk 64 [0.98 to 1.17 at 32, 1.03 to 1.33 at 48]
+// Never
+//   * above x = 256 a round, where ragged widths leave segments half empty
+//     columns: 2048 x 48 x 80 37 / 54, 4096 x 25 x 144 67 / 84;
+//   * above x = 128 where the heads' placement (heads_by_xcd) would have to be
+//     dealt out: 16384 x 18 x 176 [0.76 to 0.95, 1.00 once];
+//   * above x = 128 with fp32 inputs (4096 x 32 x 128 86.6 / 99.1), whose second
+//     kernel fits once on a CU, or with chunk states, where 32 heads fill the
+//     chip either way (16384 x 32 350 / 356; fewer heads not settled).
+inline bool linattn_in_segments(const ScanParams& p) {
+    const int64_t n = (p.T + 63) / 64, x = (int64_t)p.H * ((p.dv + 63) / 64) * 4;
+    const int per = p.dv / 16;
+    const int64_t rounds = scan_rounds(p.H, per);
+    const bool d64 = p.dk == 64 && !p.in_f32;
+    if (x <= 64) return n >= (p.in_f32 ? 8 : 16);
+    if (x <= 128) return n >= (d64 ? (x <= 96 ? 32 : 48) : p.in_f32 && x > 96 ? 32 : 28);
+    if (p.in_f32 || p.chunk_states || x > 256 * rounds) return false;
+    if (rounds > 1) return n >= (rounds > 2 || x <= 384 ? (d64 ? 48 : 32) : (d64 ? 96 : 64));
+    if (p.H > 10 && !heads_by_xcd(p.H, per)) return false;
+    if (x <= 144) return n >= 64;
+    return n >= (x <= 176 ? (d64 ? 128 : 96) : (d64 ? 256 : 128));
+}
+
+// A call in segments of G chunks (the last takes the rest), nseg of them;
+// the second launch has a workgroup per segment, head and `cols` columns.
+struct SegPlan {
+    int64_t G, nseg;
+    int cols;
+};
+constexpr int kSegWorkgroups = 512;  // two per CU (with fp32 inputs one fits: two rounds)
+inline SegPlan linattn_seg_plan(const ScanParams& p) {
+    const int64_t n = (p.T + 63) / 64;
+    SegPlan s;
+    // Columns per workgroup: 128 halve the reads of Q and K, 64 halve the time
+    // of one chunk and give twice the workgroups.  16384 tokens x 16 heads (4096
+    // workgroup-chunks of 128 columns): 153 us, with 64 columns 165; 2048 x 16
+    // (512): 34 and 31.  The line between the two is not measured.
+    s.cols = !p.in_f32 && p.dv > 64 && n * p.H * ((p.dv + 127) / 128) >= 3072 ? 128 : 64;
+    // Segments: as many as run at once (more only add hand-over traffic:
+    // 16384 x 32, 256 to 282 us with 2048 workgroups), each with at least the dk
+    // tokens that its hand-over takes in o.
+    const int64_t per = (int64_t)p.H * ((p.dv + s.cols - 1) / s.cols);
+    const int64_t want = per < kSegWorkgroups ? kSegWorkgroups / per : 1;
+    s.G = (n + want - 1) / want;
+    if (!p.chunk_states && s.G < p.dk / 64) s.G = p.dk / 64;
+    s.nseg = (n + s.G - 1) / s.G;
+    if (!p.chunk_states && s.nseg > 1 && p.T - (s.nseg - 1) * s.G * 64 < p.dk) --s.nseg;
+    return s;
+}
 
 hipError_t launch_linattn_scan(const ScanParams& p, hipStream_t stream);
 // the same call in segments of the sequence (T > 64), the same bits

@@ -753,23 +753,7 @@ hipError_t launch_t(ScanParams p, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_linattn_scan(const ScanParams& p, hipStream_t stream) {
-    // Long calls run in segments (linattn_seg.hip, the same bits), by the
-    // chunks n and by x, 4 per head and 64 columns begun: up to x = 256 (one
-    // workgroup per CU) this kernel takes 4.5 us + 0.98 us a chunk whatever x,
-    // the segments 11 us + a rate that grows with x.  Measured (us, this kernel
-    // / segments, dk = dv = 128): 1024 tokens x 8 heads 20.9 / 19.1, x 16 21.4 /
-    // 23.2; 2048 x 16 37.7 / 31.4, x 24 37.8 / 40.2; 4096 x 32 71.2 / 70.1; 16384
-    // x 1 251 / 80, x 16 256 / 153, x 32 288 / 260; above x = 256 this kernel
-    // takes a second round (2048 x 32 x 256 columns 73.4 / 67.7).  fp32 inputs:
-    // 512 x 16 x 64 columns 15.3 / 14.6, but 4096 x 32 x 128 columns 86.6 / 99.1.
-    // With chunk states both are bound by the same stores once this kernel
-    // fills the chip (16384 x 32: 350 / 356).
-    const int64_t n = (p.T + CH - 1) / CH;
-    const int x = p.H * ((p.dv + 63) / 64) * 4;
-    const int64_t from = p.in_f32 ? (x <= 64 ? 8 : x <= 128 ? 28 : INT64_MAX)
-                         : x <= 128 ? (x <= 64 ? 16 : 28)
-                         : p.chunk_states ? INT64_MAX : (x <= 256 ? 64 : 32);
-    if (n >= from) return launch_linattn_seg(p, stream);
+    if (linattn_in_segments(p)) return launch_linattn_seg(p, stream);
     // fp32 inputs keep hi and lo planes of K and V in LDS; the scan supports
     // them at dk = 64.
     if (p.dk == 128 && !p.in_f32) return launch_t<128, false>(p, stream);

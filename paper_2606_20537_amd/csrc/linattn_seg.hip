@@ -58,7 +58,6 @@ namespace {
 using namespace dev;
 
 constexpr int CH = 64;  // chunk length
-constexpr int kSegWorkgroups = 512;  // two per CU
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -855,25 +854,10 @@ template <int DK, bool F32>
 hipError_t launch_t(const ScanParams& p, hipStream_t stream) {
     SegParams sp;
     sp.s = p;
-    const int64_t n = (p.T + CH - 1) / CH;
-    // Columns per workgroup: 128 halve the reads of Q and K, 64 halve the time
-    // of one chunk and give twice the workgroups.  The line lies where both
-    // fill the chip for several chunks each (16384 tokens x 16 heads: 128
-    // columns 153 us, 64 columns 165 us; 2048 x 16: 34 and 31 us).
-    const bool nt2 = !F32 && p.dv > 64 && n * p.H * ((p.dv + 127) / 128) >= 3072;
-    const int cols = nt2 ? 128 : 64;
-    // Segments: as many as run at once, two workgroups per CU (more only add
-    // hand-over traffic: 16384 x 32, 256 to 282 us with 2048 workgroups), each
-    // with at least the dk tokens that its hand-over takes in o.
-    const int64_t per = (int64_t)p.H * ((p.dv + cols - 1) / cols);
-    const int64_t want = per < kSegWorkgroups ? kSegWorkgroups / per : 1;
-    int64_t G = (n + want - 1) / want;
-    if (!p.chunk_states && G < DK / CH) G = DK / CH;
-    int64_t nseg = (n + G - 1) / G;
-    if (!p.chunk_states && nseg > 1 && p.T - (nseg - 1) * G * CH < DK) --nseg;
-    sp.G = (int32_t)G;
-    sp.nseg = (int32_t)nseg;
-    if (nseg > 1) {
+    const SegPlan plan = linattn_seg_plan(p);
+    sp.G = (int32_t)plan.G;
+    sp.nseg = (int32_t)plan.nseg;
+    if (sp.nseg > 1) {
         // Row blocks of 64 give twice the workgroups; whole heads of 128 rows
         // halve the reads of V and of the gates once the chip is full anyway
         // (16384 x 32: 131 us; 64 rows 165 us; at 16 heads 88 and 80 us).
@@ -882,7 +866,7 @@ hipError_t launch_t(const ScanParams& p, hipStream_t stream) {
         if (e != hipSuccess) return e;
     }
     if constexpr (!F32)
-        if (nt2) return launch_seg<DK, F32, 2>(sp, stream);
+        if (plan.cols == 128) return launch_seg<DK, F32, 2>(sp, stream);
     return launch_seg<DK, F32, 1>(sp, stream);
 }
 

@@ -59,9 +59,49 @@ bool placement() {
     return true;
 }
 
+cap::ScanParams call(int64_t T, int H, int dk, int dv, bool f32, bool states) {
+    static float any;
+    cap::ScanParams p{};
+    p.T = T, p.H = H, p.dk = dk, p.dv = dv, p.in_f32 = f32, p.chunk_states = states ? &any : nullptr;
+    return p;
+}
+
+// A call in segments: they cover the chunks, each has a chunk, the dk tokens of
+// its hand-over where that lies in o, and the grid's arithmetic fits; with
+// chunk states there are several.  Shapes whose pass was the faster one, by up
+// to half, take the pass.
+bool segments() {
+    for (const int dk : {64, 128})
+        for (int f32 = 0; f32 <= (dk == 64); ++f32)
+            for (int states = 0; states < 2; ++states)
+                for (int H = 1; H <= 300; H += H < 40 ? 1 : 13)
+                    for (int dv = 16; dv <= 512; dv += 16)
+                        for (const int64_t T : {65, 128, 511, 512, 1024, 1025, 1151, 1792, 2049, 3071, 4096, 6143, 8192, 16385, 1 << 20}) {
+                            const cap::ScanParams p = call(T, H, dk, dv, f32, states);
+                            if (!cap::linattn_in_segments(p)) continue;
+                            const cap::SegPlan s = cap::linattn_seg_plan(p);
+                            const int64_t last = (s.nseg - 1) * s.G * 64, n = (T + 63) / 64;
+                            if (s.G < 1 || s.nseg < 1 || last >= T || s.nseg * s.G > 2 * n + s.G || (s.cols != 64 && s.cols != 128) ||
+                                (s.cols == 128 && f32) || (states && s.nseg < 2) ||
+                                (!states && s.nseg > 1 && (s.G * 64 < dk || T - last < dk))) {
+                                std::printf("segments: %lld x %d x %d/%d\n", (long long)T, H, dk, dv);
+                                return false;
+                            }
+                        }
+    const int pass[][4] = {{2048, 48, 128, 80}, {2048, 18, 128, 208}, {4096, 25, 128, 144}, {4096, 40, 128, 96}, {4096, 14, 128, 144},
+                           {8192, 21, 128, 176}, {16384, 24, 128, 144}, {16384, 18, 128, 176}, {1800, 32, 64, 64}, {4096, 40, 64, 80}};
+    for (const auto& c : pass)
+        if (cap::linattn_in_segments(call(c[0], c[1], c[2], c[3], false, false))) {
+            std::printf("segments: %d x %d x %d/%d is faster in one pass\n", c[0], c[1], c[2], c[3]);
+            return false;
+        }
+    return true;
+}
+
 }  // namespace
 
 int main() {
+    if (segments()) std::puts("segments ok");
     if (placement()) std::puts("placement ok");
     if (gather_shares()) std::puts("gather_shares ok");
     if (fp8_grid()) std::puts("fp8_grid ok");

@@ -22,6 +22,6 @@ def lines(tmp_path_factory):
     return subprocess.run([exe], check=True, capture_output=True, text=True, timeout=60).stdout.splitlines()
 
 
-@pytest.mark.parametrize("rule", ["fp8_grid", "gather_shares", "placement"])
+@pytest.mark.parametrize("rule", ["fp8_grid", "gather_shares", "placement", "segments"])
 def test_rule(lines, rule):
     assert rule + " ok" in lines, lines
