@@ -102,15 +102,17 @@ __device__ inline void split_n(const float* f, V& hi, V& lo) {
 
 // The same split of products f w: each is rounded once for hi and enters lo
 // exactly (one fma).  Written out, so that kernels that must agree bit for bit
-// do not depend on where the compiler contracts f w - hi.
+// do not depend on where the compiler contracts f w - hi.  The products may
+// be handed over where they are formed earlier (x).
 template <int N, typename V>
-__device__ inline void split_product(const float* f, const float* w, V& hi, V& lo) {
+__device__ inline void split_product(const float* f, const float* w, V& hi, V& lo, const float* x = nullptr) {
     static_assert(N % 2 == 0, "pairs");
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     #pragma unroll
     for (int e = 0; e < N; e += 2) {
-        const bf16x2 h = __builtin_convertvector((f32x2){f[e] * w[e], f[e + 1] * w[e + 1]}, bf16x2);
+        const f32x2 p = x ? (f32x2){x[e], x[e + 1]} : (f32x2){f[e] * w[e], f[e + 1] * w[e + 1]};
+        const bf16x2 h = __builtin_convertvector(p, bf16x2);
         const uint32_t u = __builtin_bit_cast(uint32_t, h);
         const float h0 = __builtin_bit_cast(float, u << 16);
         const float h1 = __builtin_bit_cast(float, u & 0xFFFF0000u);

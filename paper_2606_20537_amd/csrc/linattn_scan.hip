@@ -318,9 +318,11 @@ __device__ __forceinline__ void state_role(const ScanParams& p, Smem<DK, F32>& s
                 split_piece<F32>(R.vp[i], hi, lo);
                 *reinterpret_cast<bf16x8*>(&sm.v[bq][0][m * VP + jj]) = hi;
                 if (F32) *reinterpret_cast<bf16x8*>(&sm.v[bq][NL - 1][m * VP + jj]) = lo;
+                const float w[8] = {wm, wm, wm, wm, wm, wm, wm, wm};
+                float x[8];
                 #pragma unroll
-                for (int e = 0; e < 8; ++e) f[e] *= wm;
-                split_n<8>(f, hi, lo);
+                for (int e = 0; e < 8; ++e) x[e] = f[e] * wm;
+                split_product<8>(f, w, hi, lo, x);
                 *reinterpret_cast<bf16x8*>(&sm.vw[bk][0][m * VP + jj]) = hi;
                 *reinterpret_cast<bf16x8*>(&sm.vw[bk][1][m * VP + jj]) = lo;
             }
@@ -576,14 +578,19 @@ __device__ __forceinline__ void output_role(const ScanParams& p, Smem<DK, F32>& 
     auto finish = [&](int64_t c, int u, const QOp& qo, f32x4 (&at)[4]) {
         const bf16x8* qh = qo.h;
         const bf16x8* ql = qo.l;
-        // decay: factored tables below the diagonal tile, exp2 on it
+        // decay: factored tables below the diagonal tile, exp2 on it; the scores
+        // are the products at = af aw, the last of which enter the split
+        f32x4 af[4], aw[4];
         {
             const f32x4 ai = *reinterpret_cast<const f32x4*>(&sm.ai[u][i_row][0]);
             #pragma unroll
             for (int mb = 0; mb < W; ++mb) {
-                const f32x4 bmv = *reinterpret_cast<const f32x4*>(&sm.bm[u][mb * 16 + 4 * grp]);
+                aw[mb] = *reinterpret_cast<const f32x4*>(&sm.bm[u][mb * 16 + 4 * grp]);
                 #pragma unroll
-                for (int r = 0; r < 4; ++r) at[mb][r] = (at[mb][r] * ai[mb]) * bmv[r];
+                for (int r = 0; r < 4; ++r) {
+                    af[mb][r] = at[mb][r] * ai[mb];
+                    at[mb][r] = af[mb][r] * aw[mb][r];
+                }
             }
             const float gi = sm.G2[u][i_row];
             const f32x4 gm = *reinterpret_cast<const f32x4*>(&sm.G2[u][W * 16 + 4 * grp]);
@@ -591,6 +598,8 @@ __device__ __forceinline__ void output_role(const ScanParams& p, Smem<DK, F32>& 
             for (int r = 0; r < 4; ++r) {
                 const float pv = at[W][r] * __builtin_amdgcn_exp2f(gi - gm[r]);
                 at[W][r] = (4 * grp + r <= li) ? pv : 0.0f;
+                af[W][r] = at[W][r];
+                aw[W][r] = 1.0f;
             }
         }
         // O = P V, two m-blocks per MFMA (the score accumulators are P in
@@ -598,14 +607,19 @@ __device__ __forceinline__ void output_role(const ScanParams& p, Smem<DK, F32>& 
         f32x4 acc_o = {0.f, 0.f, 0.f, 0.f};
         #pragma unroll
         for (int pr = 0; 2 * pr <= W; ++pr) {
-            float f[8];
+            float x[8], f[8], w[8];
             #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                f[r] = at[2 * pr][r];
-                f[4 + r] = (2 * pr + 1 <= W) ? at[2 * pr + 1][r] : 0.0f;
+                const bool on = 2 * pr + 1 <= W;
+                x[r] = at[2 * pr][r];
+                f[r] = af[2 * pr][r];
+                w[r] = aw[2 * pr][r];
+                x[4 + r] = on ? at[2 * pr + 1][r] : 0.0f;
+                f[4 + r] = on ? af[2 * pr + 1][r] : 0.0f;
+                w[4 + r] = on ? aw[2 * pr + 1][r] : 1.0f;
             }
             bf16x8 ph, pl;
-            split_n<8>(f, ph, pl);
+            split_product<8>(f, w, ph, pl, x);
             const bf16x8 vh = cat(tr4(sm.v[u][0], VP, (2 * pr) * 16 + 4 * grp, 0, li),
                                   tr4(sm.v[u][0], VP, (2 * pr + 1) * 16 + 4 * grp, 0, li));
             acc_o = mma(ph, vh, acc_o);
@@ -646,7 +660,7 @@ __device__ __forceinline__ void output_role(const ScanParams& p, Smem<DK, F32>& 
             const f32x4 eg = *reinterpret_cast<const f32x4*>(&sm.eG[u][16 * W + 4 * grp]);
             #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float val = p.scale * (eg[r] * acc_x[r] + acc_o[r]);
+                const float val = p.scale * __builtin_fmaf(eg[r], acc_x[r], acc_o[r]);
                 __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), ro,
                                                       (uint32_t)((16 * W + 4 * grp + r) * x.o_row + ((int64_t)h * dv + j0 + li) * 4),
                                                       0, 0);
