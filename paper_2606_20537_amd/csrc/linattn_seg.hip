@@ -643,7 +643,6 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void linattn_seg_kernel(const Seg
 
     const uint32_t soff = jok ? (uint32_t)((((int64_t)h * DK + 8 * grp) * dv + jl) * 4) : kOob;
     const uint32_t ooff = jok ? (uint32_t)(4 * grp * o_row + ((int64_t)h * dv + jl) * 4) : kOob;
-    const bool cs_first = sp.nseg == 1;  // else the first launch wrote the segment's entry
     auto chunk = [&](int64_t c, auto fold) {
         const int b = (int)(c & 1);
         stage(b);
@@ -700,10 +699,10 @@ __global__ __launch_bounds__(256, F32 ? 1 : 2) void linattn_seg_kernel(const Seg
             for (int rb = 0; rb < 4; ++rb) acc[t][rb] += accl[t][rb];
 
         phase();
-        // the state entering the chunk, as chunk state c
+        // the state entering the chunk, as chunk state c (the first launch wrote
+        // the segment's first)
         if constexpr (CS) {
-            const bool w = cs_first || c > c0;
-            const rsrc_t rc = make_rsrc_u32(p.chunk_states + c * (int64_t)H * DK * dv, w ? (uint32_t)(H * DK * dv * 4) : 0u);
+            const rsrc_t rc = make_rsrc_u32(p.chunk_states + c * (int64_t)H * DK * dv, c > c0 ? (uint32_t)(H * DK * dv * 4) : 0u);
             const uint32_t so = fresh(soff);
             #pragma unroll
             for (int u = 0; u < NU; ++u)
@@ -857,6 +856,7 @@ hipError_t launch_t(const ScanParams& p, hipStream_t stream) {
     const SegPlan plan = linattn_seg_plan(p);
     sp.G = (int32_t)plan.G;
     sp.nseg = (int32_t)plan.nseg;
+    if (sp.nseg == 1 && p.chunk_states) return hipErrorInvalidValue;  // (no such call: linattn_in_segments)
     if (sp.nseg > 1) {
         // Row blocks of 64 give twice the workgroups; whole heads of 128 rows
         // halve the reads of V and of the gates once the chip is full anyway
