@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <vector>
 
 #include "internal.h"
@@ -100,7 +101,15 @@ bool segments() {
 
 }  // namespace
 
-int main() {
+int main(int argc, char** argv) {
+    if (argc == 7) {  // T H dk dv fp32 states: the plan of a linear-attention prefill
+        const cap::ScanParams p = call(std::atoll(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]),
+                                       std::atoi(argv[5]), std::atoi(argv[6]));
+        const cap::SegPlan s = cap::linattn_seg_plan(p);
+        if (cap::linattn_in_segments(p)) std::printf("%d %lld %lld\n", s.cols, (long long)s.nseg, (long long)s.G);
+        else std::puts("one pass");
+        return 0;
+    }
     if (segments()) std::puts("segments ok");
     if (placement()) std::puts("placement ok");
     if (gather_shares()) std::puts("gather_shares ok");
