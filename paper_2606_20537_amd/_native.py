@@ -139,15 +139,28 @@ def _addr(x):
     return x.data_ptr()
 
 
+_raw = None  # torch's lookups of (current stream handle of a device, current device); () without them
+
+
+def _raw_lookups(torch):
+    global _raw
+    if _raw is None:
+        fns = [getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice")]
+        _raw = tuple(fns) if all(map(callable, fns)) else ()
+    return _raw
+
+
 def _stream(s):
     if s is None:
         import torch
         # torch.cuda.current_stream() builds a Stream object: 3.0 us of the 7.8 us
         # that a decode step took the host, against 0.3 us for the handle alone.
-        # Without an initialised device it does the initialisation, or raises
-        # (a forked child).
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # It stays the way where torch has no such lookup, and without an
+        # initialised device, where it does the initialisation, or raises (a
+        # forked child).
+        raw = _raw if _raw is not None else _raw_lookups(torch)
+        if raw and torch.cuda.is_initialized():
+            return raw[0](raw[1]())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(s, int):
         return s
