@@ -38,7 +38,9 @@
  *     no device byte has been written.  CAP_E_HIP reports a launch the HIP
  *     runtime refused; in a multi-launch call (a fork into many sets, a
  *     gather of more than 64 environments, an append to more than 128
- *     buffers) the launches before it stay enqueued.
+ *     buffers, a linear-attention prefill of many chunks, a delta-rule
+ *     prefill) the launches before it stay enqueued, and what they wrote of
+ *     the outputs is not a result.
  *   - The library reads launch status from the launch calls themselves and
  *     never clears an error the caller left pending (the runtime's "last
  *     error"); it clears only the error its own pointer-attribute query
@@ -204,7 +206,7 @@ CAP_API int capsule_fork(cap_capsule cap, const cap_set* lives, uint32_t n,
  * a HOST array of n_env int32 in [0, n_gallery) (CAP_E_INVAL otherwise).
  * All gallery capsules and all environment sets must share one layout and
  * one P' and deployment key (CAP_E_SIZE / CAP_E_DIGEST); the env sets must be
- * distinct.  One launch per call for any n_env; every env set's position
+ * distinct.  One launch per 64 environments; every env set's position
  * becomes P'. */
 CAP_API int capsule_gather_restore(const cap_capsule* gallery, uint32_t n_gallery,
                                    const int32_t* ids, const cap_set* lives,
@@ -252,6 +254,11 @@ CAP_API uint64_t capsule_digest_tokens(const int32_t* ids, uint64_t n);
  * bit for bit, what one longer call computes for the same tokens.  This
  * holds for every T >= 1, so a remainder of one token re-prefilled after a
  * restore equals the cold prefill's last chunk bit for bit.
+ *
+ * One launch, or two for calls of many chunks (by their sizes; the bits are
+ * the same).  Between the two the states that enter segments of the sequence
+ * lie in chunk_states, or without them in o: during the call o's bytes mean
+ * nothing, and a call that ends with CAP_E_HIP may leave states there.
  *
  * Layouts (all contiguous, device, caller-owned):
  *   q, k : [T, H, dk]  in_dtype (bf16 or f32)      v : [T, H, dv] in_dtype
