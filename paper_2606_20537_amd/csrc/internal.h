@@ -145,49 +145,6 @@ struct ScanParams {
 // on CAP_OK *out holds the launch parameters.
 int validate_linattn(const linattn_args* a, ScanParams* out);
 
-// Whether a linear-attention prefill runs in segments of the sequence
-// (linattn_seg.hip) or in one pass (linattn_scan.hip); both give the same bits.
-// In chunks n and in x, 4 for each head and 64 columns begun: while the pass
-// takes one round it takes 4.5 us + 0.98 us a chunk whatever x, the segments
-// 11 us + a rate that grows with x.  Measured at up to 64 heads x 256 columns
-// (pass / segments, us; in brackets the range of their ratio over all shapes
-// at a number of chunks, bf16 and dk 128 where nothing is said):
-//   x <= 64    1024 tokens x 8 heads x 128 columns 20.9 / 19.1 [1.01 to 1.13 at
-//              16]; dk 64 [1.00 to 1.21]; fp32, 512 tokens [1.04 to 1.12 at 8]
-//   x <= 128   2048 x 16 x 128 37.7 / 31.4 [from 0.83 at 16, from 1.00 at 28]; dk 64
-//              [up to x = 96 from 0.97 at 28, 1.04 at 32; beyond 0.96 at 32, 1.04 at
-//              48]; fp32 [from 0.98 at 28 with 32 heads x 64, else 1.01]
-//   x <= 144   [0.89 to 1.14 at 32, 1.01 to 1.32 at 64]; dk 64 [1.07 to 1.15 at 64]
-//   x <= 176   [0.94 to 1.19 at 64, 1.02 to 1.31 at 96]; dk 64 [0.99 to 1.06 at 64,
-//              1.07 to 1.16 at 128]
-//   x <= 256   [0.92 to 1.17 at 96, 0.98 to 1.30 at 128]; dk 64 [0.93 to 1.18 at 128,
-//              1.01 to 1.40 at 256]; 16384 x 16 x 128 256 / 153, x 32 288 / 260
-//   two rounds [up to x = 384 0.99 to 1.22 at 32; beyond 0.98 to 1.06 at 32, 1.00 to
-//              1.23 at 64]; dk 64 [up to 384 1.04 to 1.21 at 48; beyond 0.95 to 1.11
-//              at 64, 1.08 to 1.29 at 128]
-//   more       [1.02 to 1.28 at 32]; dk 64 [0.98 to 1.17 at 32, 1.03 to 1.33 at 48]
-// Never
-//   * above x = 256 a round, where ragged widths leave segments half empty
-//     columns: 2048 x 48 x 80 37 / 54, 4096 x 25 x 144 67 / 84;
-//   * above x = 128 where the heads' placement (heads_by_xcd) would have to be
-//     dealt out: 16384 x 18 x 176 [0.76 to 0.95, 1.00 once];
-//   * above x = 128 with fp32 inputs (4096 x 32 x 128 86.6 / 99.1), whose second
-//     kernel fits once on a CU, or with chunk states, where 32 heads fill the
-//     chip either way (16384 x 32 350 / 356; fewer heads not settled).
-inline bool linattn_in_segments(const ScanParams& p) {
-    const int64_t n = (p.T + 63) / 64, x = (int64_t)p.H * ((p.dv + 63) / 64) * 4;
-    const int per = p.dv / 16;
-    const int64_t rounds = scan_rounds(p.H, per);
-    const bool d64 = p.dk == 64 && !p.in_f32;
-    if (x <= 64) return n >= (p.in_f32 ? 8 : 16);
-    if (x <= 128) return n >= (d64 ? (x <= 96 ? 32 : 48) : p.in_f32 && x > 96 ? 32 : 28);
-    if (p.in_f32 || p.chunk_states || x > 256 * rounds) return false;
-    if (rounds > 1) return n >= (rounds > 2 || x <= 384 ? (d64 ? 48 : 32) : (d64 ? 96 : 64));
-    if (p.H > 10 && !heads_by_xcd(p.H, per)) return false;
-    if (x <= 144) return n >= 64;
-    return n >= (x <= 176 ? (d64 ? 128 : 96) : (d64 ? 256 : 128));
-}
-
 // A call in segments of G chunks (the last takes the rest), nseg of them;
 // the second launch has a workgroup per segment, head and `cols` columns.
 struct SegPlan {
@@ -213,6 +170,67 @@ inline SegPlan linattn_seg_plan(const ScanParams& p) {
     s.nseg = (n + s.G - 1) / s.G;
     if (!p.chunk_states && s.nseg > 1 && p.T - (s.nseg - 1) * s.G * 64 < p.dk) --s.nseg;
     return s;
+}
+
+// Whether a linear-attention prefill runs in segments of the sequence
+// (linattn_seg.hip) or in one pass (linattn_scan.hip); both give the same bits.
+// In chunks n and in x, 4 for each head and 64 columns begun: while the pass
+// takes one round it takes 4.5 us + 0.98 us a chunk whatever x, the segments
+// 11 us + a rate that grows with x.  Measured at up to 64 heads x 256 columns,
+// inputs repeated and in turn (pass / segments, us; in brackets the lowest and
+// highest ratio over all shapes at a number of chunks, bf16 and dk 128 where
+// nothing is said):
+//   x <= 64    1024 tokens x 8 heads x 128 columns 20.9 / 19.1 [16: 1.01 to 1.15];
+//              dk 64 [16: 0.99 to 1.21]; fp32, 512 tokens [8: 1.04 to 1.12]
+//   x <= 128   2048 x 16 x 128 37.7 / 31.4 [16: from 0.83, 28: from 1.00]; dk 64 [up
+//              to x = 96, 28: from 0.96, 32: 1.03; beyond, 32: 0.96, 48: 1.04]; fp32
+//              [32 heads x 64, 28 to 36: 0.97 to 1.00; else 28: 1.01]
+//   x <= 144   [32: 0.88 to 1.14, 64: 1.01 to 1.40]; dk 64 [64: 1.07 to 1.15]
+//   x <= 176   [64: 0.94 to 1.40, 96: 1.02 to 1.50]; dk 64 [64: 0.99 to 1.19, 128:
+//              0.99 to 1.37]
+//   x <= 256   8192 x 32 x 128 140 / 147, 8384 x 32 x 128 as long, 16384 x 32 288 / 260,
+//              x 16 256 / 153 [96: 0.92 to 1.20, 130: from 1.00]; dk 64 [128: 0.93 to
+//              1.21, 256: 1.01 to 1.40]
+//   two rounds [up to x = 320, 32: 1.04 to 1.22; up to 384, 32: 0.94 to 1.10, 40: 1.03 to
+//              1.21; beyond, 48: 0.95 to 1.13, 64: 1.00 to 1.23]; dk 64 [up to 384, 48:
+//              1.00 to 1.23; beyond, 64: 0.95 to 1.19, 128: 1.07 to 1.30]
+//   more       [32: 1.02 to 1.28]; dk 64 [32: 0.98 to 1.21, 48: 1.03 to 1.33]
+// A last segment that takes `late` chunks more than the others (its own would
+// hold fewer than the dk tokens of a hand-over in o) holds the call up: 981
+// tokens x 6 heads x 16 columns 19.8 / 24.9; with five chunks more for each
+// nothing measured loses.
+// Never
+//   * above x = 256 a round, where ragged widths leave segments half empty
+//     columns: 2048 x 48 x 80 37 / 54, 4096 x 25 x 144 67 / 84;
+//   * above x = 128 where the heads' placement (heads_by_xcd) would have to be
+//     dealt out: 16384 x 18 x 176 [0.76 to 0.95, 1.00 once];
+//   * above x = 128 with fp32 inputs (4096 x 32 x 128 86.6 / 99.1), whose second
+//     kernel fits once on a CU, or with chunk states, where 32 heads fill the
+//     chip either way (16384 x 32 350 / 356; fewer heads not settled).
+inline bool linattn_in_segments(const ScanParams& p) {
+    const int64_t n = (p.T + 63) / 64, x = (int64_t)p.H * ((p.dv + 63) / 64) * 4;
+    if (n < 8) return false;
+    const int per = p.dv / 16;
+    const int64_t rounds = scan_rounds(p.H, per);
+    const bool d64 = p.dk == 64 && !p.in_f32;
+    int64_t from;
+    if (x <= 64) {
+        from = p.in_f32 ? 8 : 16;
+    } else if (x <= 128) {
+        from = x <= 96 ? (d64 ? 32 : 28) : d64 ? 48 : p.in_f32 ? 40 : 28;
+    } else if (p.in_f32 || p.chunk_states || x > 256 * rounds) {
+        return false;
+    } else if (rounds > 1) {
+        const bool more = rounds > 2;
+        from = more || x <= 320 ? (d64 ? 48 : 32) : x <= 384 ? (d64 ? 48 : 40) : (d64 ? 96 : 64);
+    } else if (p.H > 10 && !heads_by_xcd(p.H, per)) {
+        return false;
+    } else {
+        from = x <= 144 ? 64 : x <= 176 ? (d64 ? 128 : 96) : (d64 ? 256 : 144);
+    }
+    const SegPlan s = linattn_seg_plan(p);
+    const int64_t late = n - s.nseg * s.G;
+    return n >= from + (late > 0 ? 5 * late : 0);
 }
 
 hipError_t launch_linattn_scan(const ScanParams& p, hipStream_t stream);

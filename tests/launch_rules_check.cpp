@@ -77,11 +77,11 @@ bool segments() {
             for (int states = 0; states < 2; ++states)
                 for (int H = 1; H <= 300; H += H < 40 ? 1 : 13)
                     for (int dv = 16; dv <= 512; dv += 16)
-                        for (const int64_t T : {65, 128, 511, 512, 1024, 1025, 1151, 1792, 2049, 3071, 4096, 6143, 8192, 16385, 1 << 20}) {
+                        for (const int64_t T : {0, 1, 65, 128, 511, 512, 1024, 1025, 1151, 1792, 2049, 3071, 4096, 6143, 8192, 16385, 1 << 20}) {
                             const cap::ScanParams p = call(T, H, dk, dv, f32, states);
                             if (!cap::linattn_in_segments(p)) continue;
                             const cap::SegPlan s = cap::linattn_seg_plan(p);
-                            const int64_t last = (s.nseg - 1) * s.G * 64, n = (T + 63) / 64;
+                            const int64_t n = (T + 63) / 64, last = (s.nseg - 1) * s.G * 64;
                             if (s.G < 1 || s.nseg < 1 || last >= T || s.nseg * s.G > 2 * n + s.G || (s.cols != 64 && s.cols != 128) ||
                                 (s.cols == 128 && f32) || (states && s.nseg < 2) ||
                                 (!states && s.nseg > 1 && (s.G * 64 < dk || T - last < dk))) {
@@ -90,7 +90,8 @@ bool segments() {
                             }
                         }
     const int pass[][4] = {{2048, 48, 128, 80}, {2048, 18, 128, 208}, {4096, 25, 128, 144}, {4096, 40, 128, 96}, {4096, 14, 128, 144},
-                           {8192, 21, 128, 176}, {16384, 24, 128, 144}, {16384, 18, 128, 176}, {1800, 32, 64, 64}, {4096, 40, 64, 80}};
+                           {8192, 21, 128, 176}, {16384, 24, 128, 144}, {16384, 18, 128, 176}, {1800, 32, 64, 64}, {4096, 40, 64, 80},
+                           {8192, 32, 128, 128}, {2048, 64, 128, 128}, {981, 6, 128, 16}, {1129, 9, 128, 48}, {1366, 5, 128, 176}};
     for (const auto& c : pass)
         if (cap::linattn_in_segments(call(c[0], c[1], c[2], c[3], false, false))) {
             std::printf("segments: %d x %d x %d/%d is faster in one pass\n", c[0], c[1], c[2], c[3]);
