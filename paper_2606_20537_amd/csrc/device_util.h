@@ -1,4 +1,5 @@
-// Device helpers shared by the chunked scans (linattn_scan.hip, gdn_scan.hip):
+// Device helpers shared by the chunked scans (linattn_scan.hip, linattn_seg.hip,
+// gdn_scan.hip):
 // gfx950 MFMA, buffer resources, transposing LDS reads, a DPP wave scan,
 // hi/lo bf16 splitting and an LDS-only workgroup barrier.  Not part of the
 // public ABI.

@@ -1,7 +1,7 @@
 // Internal interface between the host ABI (capsule_host.cpp) and the HIP
-// kernels (capsule_copy.hip, linattn_scan.hip, linattn_step.hip,
-// gdn_scan.hip, gdn_step.hip, kv_fp8.hip, append.hip).  Not part of the
-// public ABI.
+// kernels (capsule_copy.hip, linattn_scan.hip, linattn_seg.hip,
+// linattn_step.hip, gdn_scan.hip, gdn_step.hip, kv_fp8.hip, append.hip), and
+// the rules that size their launches.  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime_api.h>

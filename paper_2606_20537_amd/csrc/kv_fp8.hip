@@ -11,21 +11,22 @@
 // 3 mantissa bits; subnormals m/8 * 2^-6; largest finite 448 (S.1111.110);
 // S.1111.111 is NaN; there are no infinities.  Encoding rounds to nearest,
 // ties to even, and saturates: |x| >= 448 and +-inf give +-448; NaN keeps its
-// sign.  Both conversions are exact integer / power-of-two arithmetic, so the
-// codes and the BF16 results are bit-identical to any implementation of the
-// same definition.
+// sign (the product's, x times 1 / scale).  Each conversion is one fp32 product
+// and one correctly rounded conversion instruction, so the codes and the BF16
+// results are bit-identical to any implementation of the same definition.
 //
 // Streaming, HBM-bound: a unit is 8 elements, 16 bytes of BF16 and 8 of FP8, so
 // that the lanes of a wave read and write contiguous bytes on both sides
 // (nontemporal); a thread has its two units' loads in flight before it
-// converts the first (four: 190 and 207 us at the size below, one: 222 and 218).  One grid covers up to 64 segments (one per KV buffer),
-// each block a run of 4096 elements of one segment found by a binary search
-// over the launch table.  The conversions are the hardware's (OCP on gfx950:
+// converts the first (four: 190 and 207 us at the size below, one: 222 and 218).
+// One grid covers up to 64 segments (one per KV buffer), each block a run of
+// 4096 elements of one segment found by a binary search over the launch table.
+// The conversions are the hardware's (OCP on gfx950:
 // v_cvt_pk_fp8_f32, v_cvt_pk_f32_fp8, v_cvt_pk_bf16_f32; round to nearest even),
 // with saturation in front of the encoder, which by itself would turn an
 // overflow into NaN.  In integer arithmetic they took about 20 instructions an
 // element and bound the kernel (24 buffers x 16.8 M elements: quantize 264 us,
-// dequantize 247 us; now 185 and 193 us, 6.5 and 6.3 TB/s).
+// dequantize 247 us; now 183 and 193 us in a kernel trace, 6.6 and 6.3 TB/s).
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -34,7 +35,6 @@ namespace cap {
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

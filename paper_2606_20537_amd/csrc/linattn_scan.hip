@@ -7,6 +7,9 @@
 //   o_i     = scale * (exp(G_i) q_i S_j + sum_{m<=i} exp(G_i - G_m)(q_i.k_m) v_m)
 //   S_{j+1} = exp(G_last) S_j + D_j,  D_j = sum_m exp(G_last - G_m) k_m^T v_m
 //
+// Long calls of few heads run in segments of the sequence instead
+// (linattn_seg.hip, the same bits; linattn_in_segments draws the line).
+//
 // Work split: one workgroup per (head, 16-wide slice of the value columns).
 // Column slices of S are independent: o[:, J] needs only S[:, J] and v[:, J],
 // and the fold of S[:, J] needs only v[:, J].  The workgroup walks the chunks

@@ -32,9 +32,12 @@
 //
 // Measured (us, dk = dv = 128, final state only; linattn_scan.hip / this):
 // 16384 tokens x 1 head 251 / 80, x 16 heads 256 / 153, x 32 heads 288 / 260;
-// 2048 x 16 heads 37.7 / 31.4.  At 32 heads the second launch runs at the rate
-// of its bytes (740 MB in 142 us) and the first, 131 us for 268 MB of K and V,
-// at that of the L2, which serves K to the eight workgroups of a head.
+// 2048 x 16 heads 37.7 / 31.4.  At 16384 x 32 a kernel trace gives the first
+// launch 125 and the second 141 us.  The second moves 726 MB (counters; 709 are
+// its inputs and outputs), 5.2 TB/s, with the MFMA pipe 25 % busy.  The first
+// moves 337 MB; a workgroup asks the L2, which serves K to the eight of a head,
+// for 293 lines a chunk (375 cycles on average), the texture address unit is
+// busy 70 % of the time and a SIMD issues 39 %.
 //
 // Operand layouts.  The rows that a tile stands for are free:
 //  * K^T of the fold is read with columns 32 (u / 2) + 8 (li / 4) + 4 (u % 2) +
@@ -142,9 +145,9 @@ __device__ inline bf16x8 trk(const __bf16* tile, int pitch, int k0, int u, int l
 // and hands it over in LDS; after the round's one barrier every thread runs
 // the fma chain of its elements over the round's chunks while its wave already
 // works on the next round (D is double buffered).  A round takes about 2 us
-// on an idle chip (vector arithmetic, LDS and a load's latency in turn: 5000
-// cycles, of which MFMA 512 and arithmetic 1200 per wave), 4 us when 256
-// workgroups share the L2.
+// on an idle chip, vector arithmetic, LDS and a load's latency in turn, and 4.2
+// us (10,000 cycles; a wave issues 267 vector instructions in it, 32 of them
+// MFMA of 16 cycles) when 256 workgroups share the L2.
 //
 // K never passes through LDS: lane (li, grp) loads columns NU li .. +NU - 1 of
 // the rows 32 mm + 8 grp + e, so each load takes whole rows of the head, and
@@ -253,8 +256,8 @@ __global__ __launch_bounds__(64 * kFoldWaves, 2) void linattn_fold_kernel(const 
     // the loads, which then hit in L2.  The word read is only consumed as an
     // asm operand two rounds later, forcing nothing but the load's completion.
     // Only with the whole row block in one workgroup, the shape of calls that
-    // fill the chip (there 150 -> 131 us at 16384 tokens x 32 heads); with fewer
-    // workgroups the misses overlap anyway and it costs 1 to 3 %.
+    // fill the chip (a call of 16384 tokens x 32 heads 272 -> 257 us, x 24 229 ->
+    // 214); with fewer workgroups the misses overlap anyway and it costs 1 to 3 %.
     uint32_t pf[2] = {0u, 0u};
     const char* pbase = static_cast<const char*>(p.k);
     int64_t prow = 0;  // bytes per token of the lane's line, 0: no line
@@ -860,7 +863,8 @@ hipError_t launch_t(const ScanParams& p, hipStream_t stream) {
     if (sp.nseg > 1) {
         // Row blocks of 64 give twice the workgroups; whole heads of 128 rows
         // halve the reads of V and of the gates once the chip is full anyway
-        // (16384 x 32: 131 us; 64 rows 165 us; at 16 heads 88 and 80 us).
+        // (the call, 16384 x 32: 252 us, with 64 rows 327; x 24: 214 and 296; at 16
+        // heads 174 and 166, 2048 x 16 32.5 and 30.7).
         const hipError_t e = DK == 128 && p.H * (p.dv / 16) > 128 ? launch_fold<DK, DK, F32>(sp, stream)
                                                                   : launch_fold<DK, 64, F32>(sp, stream);
         if (e != hipSuccess) return e;

@@ -39,3 +39,18 @@ def test_reciprocal_out_of_range(orc, scale):
     cap.kv_fp8_quantize([(torch.from_numpy(bits.view(np.int16).copy()).cuda(), dst, 65536, scale)])
     torch.cuda.synchronize()
     assert np.array_equal(dst.cpu().numpy(), orc.fp8_quantize(bits, scale))
+
+
+def test_every_value_in_every_position(orc):
+    """A unit converts eight elements with packed instructions: every code, and
+    every bf16 pattern, in each of the eight positions."""
+    codes = np.concatenate([np.roll(np.arange(256, dtype=np.uint8), i) for i in range(8)])
+    bits = np.concatenate([np.roll(np.arange(65536, dtype=np.uint32), i).astype(np.uint16) for i in range(8)])
+    out = torch.zeros(codes.size, dtype=torch.int16, device="cuda")
+    dst = torch.zeros(bits.size, dtype=torch.uint8, device="cuda")
+    cap.kv_fp8_dequantize([(torch.from_numpy(codes).cuda(), out, codes.size, 0.3)])
+    cap.kv_fp8_quantize([(torch.from_numpy(bits.view(np.int16).copy()).cuda(), dst, bits.size, 0.3)])
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint16), orc.fp8_dequantize(codes, 0.3))
+    want = orc.fp8_quantize(np.arange(65536, dtype=np.uint32).astype(np.uint16), 0.3)
+    assert np.array_equal(dst.cpu().numpy(), np.concatenate([np.roll(want, i) for i in range(8)]))
