@@ -206,7 +206,8 @@ inline SegPlan linattn_seg_plan(const ScanParams& p) {
 //     dealt out: 16384 x 18 x 176 [0.76 to 0.95, 1.00 once];
 //   * above x = 128 with fp32 inputs (4096 x 32 x 128 86.6 / 99.1), whose second
 //     kernel fits once on a CU, or with chunk states, where 32 heads fill the
-//     chip either way (16384 x 32 350 / 356; fewer heads not settled).
+//     chip either way (16384 x 32 350 / 356; fewer heads would gain there, up to
+//     x = 176 [96: 1.04 to 1.70], up to 256 [96: 0.95 to 1.48], and do not take it).
 inline bool linattn_in_segments(const ScanParams& p) {
     const int64_t n = (p.T + 63) / 64, x = (int64_t)p.H * ((p.dv + 63) / 64) * 4;
     if (n < 8) return false;

@@ -64,6 +64,43 @@ def test_large_segments_equal_single_chunks(T, H, dk, dv, dtype, states, with_s0
     compare(d, T, H, dk, dv, dtype, states, with_s0)
 
 
+@pytest.mark.parametrize("states", [False, True])
+def test_segments_in_a_graph(states):
+    """Both launches recorded in one graph: every replay, on new inputs and with
+    eager work in between, equals the eager call."""
+    T, H, dk, dv = 1800, 3, 128, 48
+    gen = torch.Generator(device="cuda").manual_seed(5)
+
+    def tokens():
+        q, k = (torch.nn.functional.normalize(torch.randn((T, H, dk), generator=gen, device="cuda"), dim=-1).bfloat16()
+                for _ in range(2))
+        return [q, k, torch.randn((T, H, dv), generator=gen, device="cuda").bfloat16(),
+                torch.nn.functional.logsigmoid(3 + torch.randn((T, H), generator=gen, device="cuda"))]
+
+    def outputs():
+        return [torch.full(s, float("nan"), device="cuda") for s in ((T, H, dv), (H, dk, dv), ((T + 63) // 64, H, dk, dv))]
+
+    def call(x, out):
+        cap.linattn_chunked_prefill(*x, out[0], final_state=out[1], chunk_states=out[2] if states else None)
+
+    x, out = tokens(), outputs()
+    call(x, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(x, out)
+    for _ in range(3):
+        for a, b in zip(x, tokens()):
+            a.copy_(b)
+        want = outputs()
+        call(x, want)
+        for t in out:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out[:2 + states], want))
+
+
 def compare(d, T, H, dk, dv, dtype, states, with_s0):
     kind = cap.CAP_DTYPE_F32 if dtype == "f32" else cap.CAP_DTYPE_BF16
     gen = torch.Generator(device="cuda").manual_seed(T)
