@@ -68,10 +68,10 @@ LINATTN_SRC = "paper_2606_20537_amd/csrc/linattn_scan.hip"
 SEG_SRC = "paper_2606_20537_amd/csrc/linattn_seg.hip"
 COPY_SRC = "paper_2606_20537_amd/csrc/capsule_copy.hip"
 GDN_SRC = "paper_2606_20537_amd/csrc/gdn_scan.hip"
-LINATTN_SHA = "ead12d91c7b680af276847b762ca3a584083cf09403546962f89148aa0c87a31"
+LINATTN_SHA = "699590823097ad0e24d44b6fc1c2495478c76c4e9544f911a6850c971e5f305c"
 SEG_SHA = "0b78b7fc13f7e218b78c5c7a5612f7c8ae911390021d977e9fcc9a027fbb28ea"
 COPY_SHA = "8aa883cee128bd1f0f15bfb81fae7b5905a3ae33cf1a6b736a4895855d62f56f"
-GDN_SHA = "da3c1fb0edb775539aef6da15d3f7b3c6fdd905d3b2ae5515bf52b9afadf621f"
+GDN_SHA = "efb026f205952d576e10762b2b8ff92680cdccbb18e592665e7650e2de4b4cf8"
 MEASURED_TRAFFIC = {
     "scan_cs": {"src": LINATTN_SRC, "sha256": LINATTN_SHA, "bytes": 1228509776},
     "scan_final": {"src": SEG_SRC, "sha256": SEG_SHA, "bytes": 1062808088},

@@ -726,8 +726,14 @@ __global__ __launch_bounds__(NT) void linattn_scan_kernel(const ScanParams p) {
     Ctx x;
     x.H = p.H;
     x.dv = p.dv;
+    // All arguments are read before the branch: the compiler would move most of the
+    // loads behind it, a second trip to memory (17 tokens x 16 heads 3.74 us, so 3.57).
+    __asm__ volatile(""
+                     :
+                     : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.g), "s"(p.o), "s"(p.state_in),
+                       "s"(p.chunk_states), "s"(p.final_state));
     const HeadSlice hs = head_slice(blockIdx.x, p.by_xcd, x.H, x.dv / DVS);
-    if (!hs.on) return;
+    if (__builtin_expect(!hs.on, 0)) return;
     x.h = hs.h;
     x.j0 = hs.slice * DVS;
     x.lane = tid & 63;
