@@ -99,10 +99,12 @@ hipError_t launch_gather(const GatherParams& p, hipStream_t stream);
 //    20 x 176 120 / 202; linear attention, 2048 tokens, 17 x 192 39.3 / 70.2;
 //  * where it would have half as much again as its share (1 head, 900 tokens
 //    with chunk states: 20.4 us, on one XCD 21.4; 10 heads x 256 columns, 300
-//    tokens: 12.8 and 13.7).
+//    tokens: 12.8 and 13.7);
+//  * with one slice a head, where nothing is read twice (delta-rule prefill of 17
+//    tokens, 12 heads x 16 columns: 11.5 and 11.8).
 inline bool heads_by_xcd(int H, int per) {
     const int64_t most = (H + 7) / 8, dealt = ((int64_t)H * per + 7) / 8;  // heads, workgroups of the fullest XCD
-    return H >= 8 && most * 16 <= 3 * (int64_t)H && (most * per + 31) / 32 <= (dealt + 31) / 32;
+    return H >= 8 && per > 1 && most * 16 <= 3 * (int64_t)H && (most * per + 31) / 32 <= (dealt + 31) / 32;
 }
 inline unsigned head_slice_grid(int H, int per) {
     return (unsigned)(heads_by_xcd(H, per) ? (H + 7) / 8 * 8 : H) * (unsigned)per;
@@ -229,7 +231,7 @@ inline bool linattn_in_segments(const ScanParams& p) {
     } else if (rounds > 1) {
         const bool more = rounds > 2;
         from = more || x <= 320 ? (d64 ? 48 : 32) : x <= 384 ? (d64 ? 48 : 40) : (d64 ? 96 : 64);
-    } else if (p.H > 10 && !heads_by_xcd(p.H, per)) {
+    } else if (p.H > 10 && per > 1 && !heads_by_xcd(p.H, per)) {
         return false;
     } else {
         from = x <= 144 ? 64 : x <= 176 ? (d64 ? 128 : 96) : (d64 ? 256 : 144);

@@ -44,6 +44,7 @@ bool placement() {
             const bool by_xcd = cap::heads_by_xcd(H, per);
             std::vector<int> seen((size_t)H * per), load(8);
             const unsigned grid = cap::head_slice_grid(H, per);
+            if (per == 1 && grid != (unsigned)H) return std::printf("placement: %d workgroups for %d heads\n", grid, H), false;
             for (unsigned b = 0; b < grid; ++b) {
                 const cap::HeadSlice x = cap::head_slice(b, by_xcd, H, per);
                 if (!x.on) continue;
