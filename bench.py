@@ -68,10 +68,10 @@ LINATTN_SRC = "paper_2606_20537_amd/csrc/linattn_scan.hip"
 SEG_SRC = "paper_2606_20537_amd/csrc/linattn_seg.hip"
 COPY_SRC = "paper_2606_20537_amd/csrc/capsule_copy.hip"
 GDN_SRC = "paper_2606_20537_amd/csrc/gdn_scan.hip"
-LINATTN_SHA = "699590823097ad0e24d44b6fc1c2495478c76c4e9544f911a6850c971e5f305c"
+LINATTN_SHA = "25c38bb79df22239af7f37ce3c4aa87fe00ee1c6943d10c7bfc6366d3daa070a"
 SEG_SHA = "0b78b7fc13f7e218b78c5c7a5612f7c8ae911390021d977e9fcc9a027fbb28ea"
 COPY_SHA = "8aa883cee128bd1f0f15bfb81fae7b5905a3ae33cf1a6b736a4895855d62f56f"
-GDN_SHA = "efb026f205952d576e10762b2b8ff92680cdccbb18e592665e7650e2de4b4cf8"
+GDN_SHA = "89159ecbfc6a647491aa85b3a3e1418c985bd9c8487a8b27f4b6f3275401e300"
 MEASURED_TRAFFIC = {
     "scan_cs": {"src": LINATTN_SRC, "sha256": LINATTN_SHA, "bytes": 1228509776},
     "scan_final": {"src": SEG_SRC, "sha256": SEG_SHA, "bytes": 1062808088},

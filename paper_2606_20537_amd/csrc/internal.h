@@ -118,9 +118,9 @@ struct HeadSlice {
     int h, slice;
     bool on;
 };
-// (As one count `w` over heads and slices, branched on as unlikely: computed for
-// head and slice apart, the kernels keep the scalars of their chunk loops in
-// other registers and a delta-rule prefill of 4000 tokens takes 1 to 2 % longer.)
+// (As one count `w` over heads and slices: computed for head and slice apart, the
+// delta-rule scan keeps the scalars of its chunk loop in other registers and 4000
+// tokens take 1 to 2 % longer.)
 __host__ __device__ inline HeadSlice head_slice(unsigned b, bool by_xcd, int H, int per) {
     int w = (int)b, end = H * per;
     if (by_xcd) {

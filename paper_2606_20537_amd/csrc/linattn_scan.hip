@@ -733,7 +733,7 @@ __global__ __launch_bounds__(NT) void linattn_scan_kernel(const ScanParams p) {
                      : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.g), "s"(p.o), "s"(p.state_in),
                        "s"(p.chunk_states), "s"(p.final_state));
     const HeadSlice hs = head_slice(blockIdx.x, p.by_xcd, x.H, x.dv / DVS);
-    if (__builtin_expect(!hs.on, 0)) return;
+    if (!hs.on) return;
     x.h = hs.h;
     x.j0 = hs.slice * DVS;
     x.lane = tid & 63;
