@@ -71,7 +71,7 @@ GDN_SRC = "paper_2606_20537_amd/csrc/gdn_scan.hip"
 LINATTN_SHA = "25c38bb79df22239af7f37ce3c4aa87fe00ee1c6943d10c7bfc6366d3daa070a"
 SEG_SHA = "0b78b7fc13f7e218b78c5c7a5612f7c8ae911390021d977e9fcc9a027fbb28ea"
 COPY_SHA = "8aa883cee128bd1f0f15bfb81fae7b5905a3ae33cf1a6b736a4895855d62f56f"
-GDN_SHA = "89159ecbfc6a647491aa85b3a3e1418c985bd9c8487a8b27f4b6f3275401e300"
+GDN_SHA = "fe255dd3daeca66bdca198c5356ed5a9ad05a9cb929d68084adfe704671f769f"
 MEASURED_TRAFFIC = {
     "scan_cs": {"src": LINATTN_SRC, "sha256": LINATTN_SHA, "bytes": 1228509776},
     "scan_final": {"src": SEG_SRC, "sha256": SEG_SHA, "bytes": 1062808088},

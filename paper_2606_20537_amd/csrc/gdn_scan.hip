@@ -743,9 +743,7 @@ __global__ __launch_bounds__(NT) void gdn_scan_kernel(const GdnParams p) {
                      : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.ws), "s"(p.o), "s"(p.state_in),
                        "s"(p.chunk_states), "s"(p.final_state));
     const HeadSlice hs = head_slice(blockIdx.x, p.by_xcd, x.H, x.dv / DVS);
-    // (unlikely: without the hint, other registers again; linear attention is the
-    // faster without, 16384 tokens x 32 heads with chunk states 340 us, with it 341.5)
-    if (__builtin_expect(!hs.on, 0)) return;
+    if (!hs.on) return;
     x.h = hs.h;
     x.j0 = hs.slice * DVS;
     x.lane = tid & 63;
